@@ -102,3 +102,46 @@ def test_host_layers_match_closed_forms():
         ris.swiglu(gu, m)
         g = gu.double().cpu().numpy()
         np.testing.assert_allclose(m.double().cpu().numpy(), o_model.silu(g[:, :300]) * g[:, 300:], atol=tol * 4)
+
+
+# Edges of the vector forms: one vector, a lane's last vector, one wave's
+# registers full and one vector more (four waves), four waves' registers full
+# and more (element-wise form), rows that are no whole vectors, and buffers off
+# a 16-byte boundary; row counts off the workgroup's.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols,off", [(1, 8, 0), (5, 1000, 0), (3, 1536, 0), (7, 2048, 0), (6, 2056, 0),
+                                           (2, 4096, 0), (2, 4100, 0), (3, 8192, 0), (2, 8200, 0), (5, 301, 0),
+                                           (4, 1536, 1)])
+def test_host_layers_at_vector_edges(dtype, rows, cols, off):
+    """ris_rmsnorm (residual kept bit-exact) and ris_swiglu in every form.
+
+    Bars: one rounding at the store (bf16 has 8 significant bits, so half a unit
+    in the last place is up to 2^-8 of the value; 2^-24 in float32)
+    plus the float32 arithmetic, at most 32 roundings of 2^-24: a lane adds at
+    most 32 squares and the root halves a sum's relative error, then six
+    exchanges, the root, the division and two products; swiglu has an exp (2
+    ulp), a sum, a quotient and a product."""
+    ris = need_gpu()
+    say(f"host layers {dtype} rows {rows} cols {cols} off {off}")
+    gen = torch.Generator().manual_seed(rows * 10007 + cols)
+    u = (2.0**-8 if dtype == torch.bfloat16 else 2.0**-24) + 32 * 2.0**-24
+
+    def buf(n, scale=1.0, shift=0.0):
+        b = torch.empty(n + off, dtype=dtype, device="cuda")[off:]
+        return b.copy_(torch.randn(n, generator=gen) * scale + shift)
+
+    x, r, w = buf(rows * cols).view(rows, cols), buf(rows * cols).view(rows, cols), buf(cols, 0.1, 1.0)
+    out = buf(rows * cols).view(rows, cols)
+    for res in (None, r.clone() if not off else r):
+        summed = x if res is None else (x.float() + res.float()).to(dtype)
+        ris.rmsnorm(x, w, out, 1e-6, residual=res)
+        d = summed.double()
+        want = d * torch.rsqrt(d.square().mean(-1, keepdim=True) + 1e-6) * w.double()
+        assert (out.double() - want).abs().le(u * want.abs() + 1e-30).all()
+        assert res is None or torch.equal(res, summed)
+    gu, m = buf(rows * 2 * cols, 4.0).view(rows, 2 * cols), buf(rows * cols).view(rows, cols)
+    gu[0, 0], gu[-1, cols - 1] = -200.0, 90.0                 # exp overflows; exp vanishes
+    ris.swiglu(gu, m)
+    g = gu.double()
+    want = torch.nn.functional.silu(g[:, :cols]) * g[:, cols:]
+    assert (m.double() - want).abs().le(u * want.abs() + 1e-30).all()
