@@ -20,9 +20,14 @@
 //     exchanges per tile for the max);
 //   * O += P V on MFMA with P packed to bf16 in registers and V staged
 //     row-major in wave-private LDS and read transposed (ds_read_b64_tr_b16).
-// The next tile's K/V loads issue before the current tile is computed.  Each
-// wave writes its partial (max, sum, unnormalised output); a second kernel
-// merges the partials of each (sequence, query head).
+// The next tile's K/V loads issue before the current tile is computed.  K goes
+// straight into the MFMA operand layout (64 bytes of a row per load); V, which
+// passes through LDS anyway, is loaded as whole rows (187 against 190 us for
+// 32 sequences at 64k, 16.7 against 18.4 us for one).  The four waves of a
+// workgroup merge their states in LDS and write one partial (max, sum,
+// unnormalised output) -- 1.6 instead of 6.3 MB of partials for one sequence
+// at 64k, against 35 MB of K and V --; a second kernel merges the partials of
+// each (sequence, query head).
 #include "ris_device.h"
 #include "ris_internal.h"
 
@@ -54,7 +59,7 @@ __device__ __forceinline__ int64_t key_of(const RowSegs& r, int64_t v) {
 template <int D>
 struct KVTile {
     u32x4_t k[2][D / 32];
-    u32x4_t v[2][D / 32];
+    u32x4_t v[2][D / 32];  // V rows, D / 8 lanes to a row: v[kb][s] is row 16 kb + (512 / D) s + lane / (D / 8)
     uint32_t valid;       // bit 16 kb + i: key slot 16 kb + i is a real key
 };
 
@@ -68,11 +73,14 @@ __device__ __forceinline__ void load_tile(const RowSegs& r, const uint16_t* Kr, 
         vm |= (uint32_t)(__ballot(j >= 0) & 0xFFFFull) << (16 * kb);
         const int64_t jj = j >= 0 ? j : 0;              // row 0 always exists
         const uint16_t* kp = Kr + jj * D + 8 * lg;
-        const uint16_t* vp = Vr + jj * D + 8 * lg;
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) T.k[kb][s] = *reinterpret_cast<const u32x4_t*>(kp + 32 * s);
+        constexpr int LPR = D / 8, KPI = 64 / LPR;      // lanes per V row, V rows per load
+        const int lane = li + 16 * lg;                  // max_len <= 2^31: a key fits 32 bits
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) {
-            T.k[kb][s] = *reinterpret_cast<const u32x4_t*>(kp + 32 * s);
-            T.v[kb][s] = *reinterpret_cast<const u32x4_t*>(vp + 32 * s);
+            const int jv = __shfl((int)jj, KPI * s + lane / LPR);
+            T.v[kb][s] = *reinterpret_cast<const u32x4_t*>(Vr + (int64_t)jv * D + 8 * (lane % LPR));
         }
     }
     T.valid = vm;
@@ -84,6 +92,8 @@ __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeP
     constexpr int DB = D / 16;         // 16-dim blocks of the output
     constexpr int VS = D + 16;         // V row stride in LDS (bf16 elements)
     __shared__ __align__(16) uint16_t vlds[kDecodeWaves * kTileKeys * VS];
+    __shared__ float2 ml[kDecodeWaves][8];   // the waves' (max, sum) per head
+    static_assert(kTileKeys * VS * sizeof(uint16_t) >= 8 * D * sizeof(float), "a wave's outputs fit its V slice");
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lg = lane >> 4;
@@ -140,12 +150,12 @@ __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeP
             const bool more = v0 + stride < total;
             if (more) load_tile<D>(r, Kr, Vr, v0 + stride, li, lg, nxt);
 
-            // V rows into this wave's LDS, row-major (key slot 16 kb + l%16).
+            // V rows into this wave's LDS, row-major.
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int s = 0; s < SL; ++s)
-                    *reinterpret_cast<u32x4_t*>(vw + (16 * kb + li) * VS + 32 * s + 8 * lg) = cur.v[kb][s];
+                    *reinterpret_cast<u32x4_t*>(vw + (16 * kb + (512 / D) * s + lane / (D / 8)) * VS + 8 * (lane % (D / 8))) = cur.v[kb][s];
 
             // S^T = K Q^T: lane l holds head l%16 at key slots 16 kb + 4 (l/16) + i.
             f32x4_t st[2];
@@ -211,69 +221,102 @@ __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeP
         }
     }
 
-    // ---- this wave's partial
+    // ---- the workgroup's partial: the four waves' states merged in LDS (each
+    // wave's V slice is free once its own last tile is done, but the merge's
+    // rows span other waves' slices, hence the first barrier)
     l_run = quad_sum16(l_run);
-    const int64_t slot = (int64_t)row * p.parts + part;
-    float* pml = p.part_ml + slot * G * 2;
-    if (lane < G) {
-        pml[2 * lane] = m_run;
-        pml[2 * lane + 1] = l_run;
-    }
-    float* po = p.part_o + slot * G * D;
+    __syncthreads();
+    float* ow = reinterpret_cast<float*>(vlds);             // [wave][head][dim]
+    if (lane < G) ml[wave][lane] = make_float2(m_run, l_run);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int h = 4 * lg + i;
         if (h < G) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db) po[h * D + 16 * db + li] = o[db][i];
+            for (int db = 0; db < DB; ++db) ow[(wave * G + h) * D + 16 * db + li] = o[db][i];
+        }
+    }
+    __syncthreads();
+    const int64_t slot = (int64_t)row * gridDim.x + blockIdx.x;
+    float* pml = p.part_ml + slot * G * 2;
+    float* po = p.part_o + slot * G * D;
+    for (int e = threadIdx.x; e < G * D; e += 64 * kDecodeWaves) {
+        const int h = e / D;
+        float M = ml[0][h].x;
+#pragma unroll
+        for (int w = 1; w < kDecodeWaves; ++w) M = fmaxf(M, ml[w][h].x);
+        float O = 0.f, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kDecodeWaves; ++w) {
+            const float c = __builtin_amdgcn_exp2f(ml[w][h].x - M);
+            O += c * ow[w * G * D + e];
+            L += c * ml[w][h].y;
+        }
+        po[e] = O;
+        if (e % D == 0) {
+            pml[2 * h] = M;
+            pml[2 * h + 1] = L;
         }
     }
 }
 
-// Merge the partials of one (sequence, query head), one thread per dim: the
-// threads first find the common max and each partial's weight together (in
-// LDS), then every thread sums its dim over the partials.
+// Merge the workgroups' partials of one (sequence, query head): the threads first find the
+// common max and each partial's weight together (in LDS); then D/4 lanes of
+// four dims each sum over every kGroups-th partial, and the groups' sums meet
+// in LDS.  Latency-bound (a batch of one has 256 partials of 512 bytes a head):
+// one thread per dim walking every partial took 48 us there.
+constexpr int kCombineThreads = 256;
 template <int D>
-__global__ __launch_bounds__(D) void k_decode_combine(DecodeParams p) {
-    __shared__ float wgt[kDecodeMaxParts];
-    __shared__ float red[D / 64][2];
-    const int d = threadIdx.x, lane = d & 63, wv = d >> 6;
+__global__ __launch_bounds__(kCombineThreads) void k_decode_combine(DecodeParams p, int parts) {
+    constexpr int kLanes = D / 4, kGroups = kCombineThreads / kLanes;
+    __shared__ float wgt[kDecodeMaxParts / kDecodeWaves];
+    __shared__ float red[kCombineThreads / 64][2];
+    __shared__ __align__(16) float osum[kGroups][D];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t bh = blockIdx.x;
     const int b = (int)(bh / p.Hq), h = (int)(bh % p.Hq);
     const int g = h / p.G, hh = h - g * p.G;
     const int64_t row = (int64_t)b * p.Hkv + g;
-    const int64_t step_ml = (int64_t)p.G * 2, step_o = (int64_t)p.G * D;
-    const float* ml = p.part_ml + row * p.parts * step_ml + 2 * hh;
-    const float* po = p.part_o + row * p.parts * step_o + (int64_t)hh * D + d;
+    const int64_t step_ml = p.G, step_o = (int64_t)p.G * D;
+    const float2* ml = reinterpret_cast<const float2*>(p.part_ml) + row * parts * step_ml + hh;
+    const float* po = p.part_o + row * parts * step_o + (int64_t)hh * D;
     float M = kNegBig;
-    for (int i = d; i < p.parts; i += D) M = fmaxf(M, ml[i * step_ml]);
+    for (int i = tid; i < parts; i += kCombineThreads) M = fmaxf(M, ml[i * step_ml].x);
     M = wave_max(M);
     if (lane == 0) red[wv][0] = M;
     __syncthreads();
-    M = red[0][0];
 #pragma unroll
-    for (int w = 1; w < D / 64; ++w) M = fmaxf(M, red[w][0]);
+    for (int w = 0; w < kCombineThreads / 64; ++w) M = fmaxf(M, red[w][0]);
     float L = 0.f;
-    for (int i = d; i < p.parts; i += D) {
-        const float w = __builtin_amdgcn_exp2f(ml[i * step_ml] - M);
+    for (int i = tid; i < parts; i += kCombineThreads) {
+        const float2 x = ml[i * step_ml];
+        const float w = __builtin_amdgcn_exp2f(x.x - M);
         wgt[i] = w;
-        L += w * ml[i * step_ml + 1];
+        L += w * x.y;
     }
     L = wave_sum(L);
     if (lane == 0) red[wv][1] = L;
     __syncthreads();
-    L = red[0][1];
-#pragma unroll
-    for (int w = 1; w < D / 64; ++w) L += red[w][1];
-    float O = 0.f;
+    const int grp = tid / kLanes, d4 = 4 * (tid % kLanes);
+    f32x4_t O = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
-    for (int i = 0; i < p.parts; ++i) O += wgt[i] * po[i * step_o];
-    const float y = L > 0.f ? O / L : 0.f;
-    const int64_t at = bh * D + d;
-    if (p.out_bf16)
-        static_cast<uint16_t*>(p.out)[at] = f32_to_bf16(y);
-    else
-        static_cast<float*>(p.out)[at] = y;
+    for (int i = grp; i < parts; i += kGroups) O += wgt[i] * *reinterpret_cast<const f32x4_t*>(po + i * step_o + d4);
+    *reinterpret_cast<f32x4_t*>(&osum[grp][d4]) = O;
+    __syncthreads();
+    if (tid < D) {
+        L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kCombineThreads / 64; ++w) L += red[w][1];
+        float y = 0.f;
+#pragma unroll
+        for (int k = 0; k < kGroups; ++k) y += osum[k][tid];
+        y = L > 0.f ? y / L : 0.f;
+        const int64_t at = bh * D + tid;
+        if (p.out_bf16)
+            static_cast<uint16_t*>(p.out)[at] = f32_to_bf16(y);
+        else
+            static_cast<float*>(p.out)[at] = y;
+    }
 }
 
 template <int D>
@@ -283,7 +326,8 @@ hipError_t launch_d(const DecodeParams& p, float c, hipStream_t st) {
     hipLaunchKernelGGL(k_decode_partial<D>, grid, dim3(64 * kDecodeWaves), 0, st, p, c);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_decode_combine<D>, dim3((unsigned)((int64_t)p.B * p.Hq)), dim3(D), 0, st, p);
+    hipLaunchKernelGGL(k_decode_combine<D>, dim3((unsigned)((int64_t)p.B * p.Hq)), dim3(kCombineThreads), 0, st, p,
+                       p.parts / kDecodeWaves);
     return hipGetLastError();
 }
 

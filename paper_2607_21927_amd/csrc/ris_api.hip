@@ -298,7 +298,8 @@ int ris_sparse_attn(const void* Q, const void* K, const void* V, const int64_t* 
 
 namespace {
 
-// Partials (waves) per row.  Any value covers every key (the tiles are dealt
+// Waves per row (the workspace has room for a partial of each; a workgroup's
+// waves write one together).  Any value covers every key (the tiles are dealt
 // round-robin); this one aims at ~2048 resident waves over the batch without
 // giving a wave less than one tile of a typical row (the anchor slice shared
 // evenly by the kv heads, plus window and initial tokens).

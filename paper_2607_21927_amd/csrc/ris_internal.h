@@ -90,7 +90,7 @@ hipError_t launch_attn_tile(const AttnParams& a, hipStream_t st);
 
 // Decode step (Hybrid Anchor).  Each row's virtual key list is cut into
 // kDecodeTileKeys-key tiles dealt round-robin to the row's `parts` waves
-// (kDecodeWaves per workgroup); every wave writes one partial (its max, sum
+// (kDecodeWaves per workgroup); every workgroup writes one partial (its max, sum
 // and unnormalised output per head).
 constexpr int kDecodeWaves = 4;
 constexpr int kDecodeTileKeys = 32;
@@ -104,13 +104,13 @@ struct DecodeParams {
     const int64_t* anchor_ptr;    // [B, Hkv + 1]
     const int32_t* anchor_idx;    // [B, anchor_stride]
     void* out;                    // [B, Hq, D]
-    float* part_o;                // [B * Hkv, parts, G, D]
-    float* part_ml;               // [B * Hkv, parts, G, 2]
+    float* part_o;                // [B * Hkv, parts / kDecodeWaves, G, D]
+    float* part_ml;               // [B * Hkv, parts / kDecodeWaves, G, 2]
     int64_t max_len, anchor_stride;
     int32_t B, Hq, Hkv, G, D;
     int32_t out_bf16;
     int32_t window, sink;
-    int32_t parts;                // partials per row (a multiple of kDecodeWaves)
+    int32_t parts;                // waves per row (a multiple of kDecodeWaves)
     float scale;
 };
 hipError_t launch_decode(const DecodeParams& p, hipStream_t st);

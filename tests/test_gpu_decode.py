@@ -146,6 +146,17 @@ def test_decode_matches_oracle(case):
         assert err <= tight_tol(vmax)
 
 
+# Workgroup partials per row at the edges of the merge's lane groups (8 groups
+# at D = 128, 16 at D = 64): 1, 7, 8, 9, 16, 17, and the most there are (256,
+# where some waves take a second tile).
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("window", [1, 896, 1024, 1152, 2048, 2176, 33000])
+def test_decode_partial_counts(window, D):
+    say(f"decode partials window {window} D {D}")
+    got, want, vmax = run_decode(5, 1, D, 0, 1, 1, 0, window, 0, [3], [window + 40], window + 50)
+    assert float(np.abs(got - want).max()) <= tight_tol(vmax)
+
+
 def test_decode_out_of_range_positions_give_zeros():
     got, want, _ = run_decode(12, 2, 128, 0, 10_000, 10, 0, 128, 4, [500, 500, 500],
                               [-1, 600, 700], 700, "f32")
