@@ -1,8 +1,9 @@
 // Geometry kernels: per-row key sets of the seed ensemble, emitted as CSR.
 //
-// Each row (kv_head, q) is built by one workgroup.  The row's pool is a
+// Each row (kv_head, q) is built by one group of threads: a workgroup, or a
+// wave where rows are light.  The row's pool is a
 // bitmap in LDS; every (seed, draw) pair of the ensemble is spread over the
-// 256 lanes, each lane evaluates the keyed permutation and ORs its key into
+// group's lanes, each lane evaluates the keyed permutation and ORs its key into
 // the bitmap.
 // The bitmap *is* the union over seeds (the paper merges every seed into one
 // master set and discards the seed; Methods, "Memory-Bounded Geometry
@@ -12,11 +13,12 @@
 //
 // Two-pass build: the count pass writes each row's size (popcount) to
 // row_ptr[r + 1], a single-workgroup scan turns sizes into offsets, and the
-// fill pass regenerates the bitmap and places every key by a block-wide prefix
+// fill pass regenerates the bitmap and places every key by a group-wide prefix
 // over word popcounts; rows are launched in descending q (their cost grows
 // with q) so the heavy rows start first.  One-pass build (col_idx sized from
-// the closed-form bound): a persistent grid builds every bitmap once and
-// finds each row's offset by a decoupled look-back (see k_mask_fused).
+// the closed-form bound): every bitmap is built once and each row's offset found
+// by a decoupled look-back, in a persistent grid for heavy rows (k_mask_fused)
+// and in chunks of rows for light and for few ones (k_mask_chunk).
 #include "ris_device.h"
 #include "ris_internal.h"
 #include "lookback.h"
@@ -25,15 +27,44 @@ namespace ris {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kSeedBatch = 256;  // row words of this many seeds live in LDS at once
-// A lane's slice of a batch, ceil(seeds * draws / kThreads) draws, is then at
-// most one seed's draws long: it spans at most one seed boundary.
-static_assert(kSeedBatch <= kThreads, "a lane's slice of a batch must not exceed one seed's draws");
 
-// LDS words of the seed batch's row words: a batch never holds more than
-// min(n_seeds, kSeedBatch) seeds.
+// A row is built by a group of T threads: one wave (T = 64, several rows to a
+// workgroup), or a whole workgroup (T = 256 or 1,024).
+template <int T>
+__device__ __forceinline__ int group_tid() {
+    return T == 64 ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
+}
+// Orders the group's LDS accesses.  A wave's LDS operations execute in order,
+// so a wave only needs the compiler to keep them so.
+template <int T>
+__device__ __forceinline__ void group_sync() {
+    if constexpr (T == 64) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
+// Seeds are taken in batches whose row words live in LDS at once: as few
+// batches as kSeedBatch allows, of equal size where a wave's are small.  A lane's slice of a batch,
+// ceil(seeds * draws / T) draws, is then at most one seed's draws long: it
+// spans at most one seed boundary.
+template <int T> constexpr int kSeedBatch = T < 256 ? 64 : 256;
+static_assert(kSeedBatch<64> <= 64 && kSeedBatch<256> <= 256, "a lane's slice of a batch must not exceed one seed's draws");
+template <int T>
+__host__ __device__ __forceinline__ int seed_batch(int n_seeds) {
+    if constexpr (T == 64) {
+        const int n = (n_seeds + kSeedBatch<T> - 1) / kSeedBatch<T>;
+        return (n_seeds + n - 1) / n;
+    }
+    return n_seeds < kSeedBatch<T> ? n_seeds : kSeedBatch<T>;
+}
+
+// LDS words of the seed batch's row words.
+template <int T>
 __host__ __device__ __forceinline__ int64_t rks_words(const MaskParams& p) {
-    return (int64_t)(p.n_seeds < kSeedBatch ? p.n_seeds : kSeedBatch) * kRowWords;
+    return (int64_t)seed_batch<T>(p.n_seeds) * kRowWords;
 }
 
 // Bitmap words of the largest pool of the built rows: q0 + nq keys (causal)
@@ -41,6 +72,12 @@ __host__ __device__ __forceinline__ int64_t rks_words(const MaskParams& p) {
 __host__ __device__ __forceinline__ int64_t bitmap_words(const MaskParams& p) {
     const int64_t span = p.causal ? p.q0 + p.nq : p.N;
     return (span + 31) / 32;
+}
+
+// LDS words of one group's slice: row words and bitmap, whole 16-byte pieces.
+template <int T>
+__host__ __device__ __forceinline__ int64_t group_words(const MaskParams& p) {
+    return (rks_words<T>(p) + bitmap_words(p) + 3) & ~(int64_t)3;
 }
 
 struct RowGeom {
@@ -98,12 +135,12 @@ __device__ __forceinline__ void split_draw(uint32_t idx, uint32_t draws, float i
 // to j), and every iteration advances an unfinished draw, so (slice length)
 // * size iterations bound the loop; the bound, from the longest slice, is
 // the same in every lane, so the counter lives in scalar registers.
-template <int ROUNDS>
+template <int ROUNDS, int T>
 __device__ __forceinline__ void walk_draws(const FeistelDomain& dom, const uint32_t* rks,
                                            uint32_t* bits, uint32_t total, uint32_t draws,
                                            float inv_draws) {
-    const uint32_t per = (total + kThreads - 1) / kThreads;
-    const uint32_t lo = threadIdx.x * per;
+    const uint32_t per = (total + T - 1) / T;
+    const uint32_t lo = group_tid<T>() * per;
     const uint32_t hi = min(lo + per, total);
     if (lo >= hi) return;
     // Walker A takes the lane's draws from the front, walker B from the back;
@@ -192,7 +229,7 @@ __device__ __forceinline__ void walk_draws(const FeistelDomain& dom, const uint3
 // counts the lane's draws that neither walker has started: a walker that
 // finishes a draw takes the next one from its end if rem was positive, and
 // stops otherwise (rem may go below zero once both have stopped).  A lane's
-// slice spans at most one seed boundary (kSeedBatch <= kThreads): a walker
+// slice spans at most one seed boundary (kSeedBatch <= T): a walker
 // that crosses it moves into the other walker's seed and copies that walker's
 // round keys from the other half of KM and KX.  The set of draws and each
 // draw's walk are those of walk_draws, so the bitmap is identical.
@@ -216,12 +253,12 @@ __device__ __forceinline__ bool step_down_wraps(uint32_t& J) {
     return __builtin_amdgcn_inverse_ballot_w64(borrow);
 }
 
-template <int ROUNDS>
+template <int ROUNDS, int T>
 __device__ __forceinline__ void walk_draws16(const FeistelDomain& dom, const uint32_t* rks,
                                              uint32_t* bits, uint32_t total, uint32_t draws,
                                              float inv_draws) {
-    const uint32_t per = (total + kThreads - 1) / kThreads;
-    const uint32_t lo = threadIdx.x * per;
+    const uint32_t per = (total + T - 1) / T;
+    const uint32_t lo = group_tid<T>() * per;
     const uint32_t hi = min(lo + per, total);
     if (lo >= hi) return;
     bool actA = true, actB = hi - lo >= 2;
@@ -310,67 +347,92 @@ __device__ __forceinline__ uint32_t range_bits(uint32_t w, uint32_t lo, uint32_t
 // initial-token anchor clipped to the pool (above the pool they lie inside the
 // Structural clique, which is emitted as a range of its own).  Ends with a
 // block barrier.
+// Row words of seed s of row (h, q) into LDS.
+__device__ __forceinline__ void store_row_words(const MaskParams& p, int s, int64_t q, int h, uint32_t* dst) {
+    uint32_t w[kRowWords];
+    row_round_keys(p.seed + (uint64_t)s, (uint64_t)q, (uint64_t)h, (uint64_t)p.layer, w);
+    *reinterpret_cast<u32x4_t*>(dst) = u32x4_t{w[0], w[1], w[2], w[3]};
+    *reinterpret_cast<u32x4_t*>(dst + 4) = u32x4_t{w[4], w[5], w[6], w[7]};
+}
+
+// With `have_words` (one batch of seeds) the row words are in rks already.
+template <int T>
 __device__ void build_row_bitmap(const MaskParams& p, int64_t q, int h, const RowGeom& g,
-                                 uint32_t* rks, uint32_t* bits) {
-    const int tid = threadIdx.x;
+                                 uint32_t* rks, uint32_t* bits, bool have_words = false) {
+    const int tid = group_tid<T>();
     const uint32_t W = (g.pool + 31u) >> 5;
-    const uint32_t qe = (uint32_t)q + 1u;
-    const uint32_t a_hi = min((uint32_t)p.anchor, min(qe, g.pool));
-    const uint32_t w_lo = p.window > 0 && (uint32_t)p.window < qe ? qe - (uint32_t)p.window : 0u;
-    const uint32_t w_hi = p.window > 0 ? min(qe, g.pool) : 0u;
-    for (uint32_t w = tid; w < W; w += kThreads)
-        bits[w] = range_bits(w, 0u, a_hi) | range_bits(w, w_lo, w_hi);
+    // (The persistent grid has no scalar registers to spare for the choice.)
+    if (T == 256 || (p.window | p.anchor) != 0) {
+        const uint32_t qe = (uint32_t)q + 1u;
+        const uint32_t a_hi = min((uint32_t)p.anchor, min(qe, g.pool));
+        const uint32_t w_lo = p.window > 0 && (uint32_t)p.window < qe ? qe - (uint32_t)p.window : 0u;
+        const uint32_t w_hi = p.window > 0 ? min(qe, g.pool) : 0u;
+        for (uint32_t w = tid; w < W; w += T) bits[w] = range_bits(w, 0u, a_hi) | range_bits(w, w_lo, w_hi);
+    } else {
+        for (uint32_t w = tid; w < W; w += T) bits[w] = 0u;
+    }
     if (g.draws == 0) {
-        __syncthreads();
+        group_sync<T>();
         return;
     }
     const FeistelDomain dom = make_domain(g.pool);
     const float inv_draws = 1.0f / (float)g.draws;
     // Batches keep the flat (seed, draw) index below 2^24 for the float split.
-    const int batch = (int)min((uint32_t)kSeedBatch, (1u << 24) / g.draws);
+    const int batch = (int)min((uint32_t)(T == 64 ? seed_batch<T>(p.n_seeds) : kSeedBatch<T>), (1u << 24) / g.draws);
     for (int s0 = 0; s0 < p.n_seeds; s0 += batch) {
         const int sb = min(batch, p.n_seeds - s0);
-        __syncthreads();   // bitmap cleared / previous batch's keys no longer read
+        group_sync<T>();   // bitmap cleared / previous batch's keys no longer read
         // Row words of the batch's seeds, one Philox evaluation per lane.
-        for (int t = tid; t < sb; t += kThreads) {
-            uint32_t w[kRowWords];
-            row_round_keys(p.seed + (uint64_t)(s0 + t), (uint64_t)q, (uint64_t)h, (uint64_t)p.layer, w);
-            *reinterpret_cast<u32x4_t*>(&rks[t * kRowWords]) = u32x4_t{w[0], w[1], w[2], w[3]};
-            *reinterpret_cast<u32x4_t*>(&rks[t * kRowWords + 4]) = u32x4_t{w[4], w[5], w[6], w[7]};
+        if (!have_words || s0 > 0) {
+            for (int t = tid; t < sb; t += T) store_row_words(p, s0 + t, q, h, &rks[t * kRowWords]);
         }
-        __syncthreads();
+        group_sync<T>();
         const uint32_t total = (uint32_t)sb * g.draws;
         if (dom.size <= 65536u && g.draws < 65536u) {
             if (dom.rounds == 6)
-                walk_draws16<6>(dom, rks, bits, total, g.draws, inv_draws);
+                walk_draws16<6, T>(dom, rks, bits, total, g.draws, inv_draws);
             else
-                walk_draws16<12>(dom, rks, bits, total, g.draws, inv_draws);
+                walk_draws16<12, T>(dom, rks, bits, total, g.draws, inv_draws);
         } else {
-            walk_draws<6>(dom, rks, bits, total, g.draws, inv_draws);
+            walk_draws<6, T>(dom, rks, bits, total, g.draws, inv_draws);
         }
     }
-    __syncthreads();
+    group_sync<T>();
 }
 
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* red) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+// Sum of v over the group.
+template <int T>
+__device__ __forceinline__ uint32_t group_sum(uint32_t v, uint32_t* red) {
     v = wave_sum_u32(v);
+    if constexpr (T == 64) return v;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) red[wid] = v;
     __syncthreads();
-    const uint32_t t = red[0] + red[1] + red[2] + red[3];
+    uint32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) t += red[w];
     __syncthreads();
     return t;
 }
 
-// Exclusive prefix of v over the block; *total receives the block sum.
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* red, uint32_t* total) {
+// Exclusive prefix of v over the group; *total receives the group's sum.
+template <int T>
+__device__ __forceinline__ uint32_t group_exclusive_scan(uint32_t v, uint32_t* red, uint32_t* total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const uint32_t inc = wave_inclusive_scan(v);
+    if constexpr (T == 64) {
+        *total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        return inc - v;
+    }
     if (lane == 63) red[wid] = inc;
     __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < wid; ++w) before += red[w];
-    *total = red[0] + red[1] + red[2] + red[3];
+    uint32_t before = 0, sum = 0;
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) {
+        before += w < wid ? red[w] : 0u;
+        sum += red[w];
+    }
+    *total = sum;
     __syncthreads();
     return before + inc - v;
 }
@@ -382,17 +444,18 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* r
 // the last one to three with an 8- and a 4-byte store: the store
 // instructions, whose address processing limits this loop, are about a
 // quarter of one key per store.
-__device__ void emit_row(const uint32_t* bits, uint32_t W, int32_t* out, int64_t limit, const RowGeom& g,
-                         uint32_t* red, int64_t count) {
+template <int T>
+__device__ void emit_row(const uint32_t* bits, uint32_t W, int32_t* out, int64_t limit, uint32_t clique_start,
+                         uint32_t clique_len, uint32_t* red, int64_t count) {
     // The whole row fits below limit in every valid build; the guarded path
     // is for a truncated or inconsistent row_ptr.
     const bool whole = limit >= count;
     uint32_t done = 0;
-    for (uint32_t w0 = 0; w0 < W; w0 += kThreads) {
-        const uint32_t w = w0 + threadIdx.x;
+    for (uint32_t w0 = 0; w0 < W; w0 += T) {
+        const uint32_t w = w0 + group_tid<T>();
         uint32_t word = w < W ? bits[w] : 0u;
         uint32_t total;
-        const uint32_t pos0 = done + block_exclusive_scan(__popc(word), red, &total);
+        const uint32_t pos0 = done + group_exclusive_scan<T>(__popc(word), red, &total);
         const int32_t k0 = (int32_t)(w * 32u);
         auto next_key = [&]() {
             const uint32_t b = (uint32_t)__builtin_ctz(word);   // v_ffbl_b32 (word != 0 here)
@@ -444,57 +507,79 @@ __device__ void emit_row(const uint32_t* bits, uint32_t W, int32_t* out, int64_t
         }
         done += total;
     }
-    for (uint32_t t = threadIdx.x; t < g.clique_len; t += kThreads) {
+    for (uint32_t t = group_tid<T>(); t < clique_len; t += T) {
         const int64_t pos = (int64_t)done + t;
-        if (pos < limit) out[pos] = (int32_t)(g.clique_start + t);
+        if (pos < limit) out[pos] = (int32_t)(clique_start + t);
     }
 }
 
-// Workgroup -> (row r, query q, head h), heavy (late) rows first.
-__device__ __forceinline__ void row_of_block(const MaskParams& p, int64_t& r, int64_t& q, int& h) {
-    const int64_t i = blockIdx.x;
+// Set bits of the row's W words, over the group.
+template <int T>
+__device__ __forceinline__ uint32_t row_popcount(const uint32_t* bits, uint32_t W, uint32_t* red) {
+    uint32_t c = 0;
+    for (uint32_t w = group_tid<T>(); w < W; w += T) c += __popc(bits[w]);
+    return group_sum<T>(c, red);
+}
+
+// The group's index in the launch: a workgroup for T = 256, a wave for T = 64
+// (uniform, so that the row's arithmetic is scalar).
+template <int T>
+__device__ __forceinline__ int64_t group_index() {
+    if constexpr (T == 64)
+        return (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    return blockIdx.x;
+}
+
+// The group's LDS slice: the seed batch's row words, then the row's bitmap.
+template <int T>
+__device__ __forceinline__ uint32_t* group_smem(const MaskParams& p, uint32_t* smem) {
+    if constexpr (T == 64)
+        return smem + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * group_words<T>(p);
+    return smem;
+}
+
+// Group -> (row r, query q, head h), heavy (late) rows first; false past the last row.
+__device__ __forceinline__ bool row_of_group(const MaskParams& p, int64_t i, int64_t& r, int64_t& q, int& h) {
     const int64_t local = p.nq - 1 - i / p.heads;
     h = (int)(i % p.heads);
     q = p.q0 + local;
     r = (int64_t)h * p.nq + local;
+    return local >= 0;
 }
 
+template <int T>
 __global__ __launch_bounds__(kThreads) void k_mask_count(MaskParams p, int64_t* row_ptr) {
     extern __shared__ __align__(16) uint32_t smem[];
-    __shared__ uint32_t red[4];
-    uint32_t* rks = smem;
-    uint32_t* bits = smem + rks_words(p);
+    __shared__ uint32_t red[kThreads / 64];
+    uint32_t* rks = group_smem<T>(p, smem);
+    uint32_t* bits = rks + rks_words<T>(p);
     int64_t r, q; int h;
-    row_of_block(p, r, q, h);
+    if (!row_of_group(p, group_index<T>(), r, q, h)) return;      // a whole wave
     const RowGeom g = row_geometry(p, q);
-    build_row_bitmap(p, q, h, g, rks, bits);
-    const uint32_t W = (g.pool + 31u) >> 5;
-    uint32_t c = 0;
-    for (uint32_t w = threadIdx.x; w < W; w += kThreads) c += __popc(bits[w]);
-    const uint32_t total = block_sum(c, red);
-    if (threadIdx.x == 0) row_ptr[r + 1] = (int64_t)total + g.clique_len;
+    build_row_bitmap<T>(p, q, h, g, rks, bits);
+    const uint32_t total = row_popcount<T>(bits, (g.pool + 31u) >> 5, red);
+    if (group_tid<T>() == 0) row_ptr[r + 1] = (int64_t)total + g.clique_len;
 }
 
+template <int T>
 __global__ __launch_bounds__(kThreads) void k_mask_fill(MaskParams p, const int64_t* row_ptr,
                                                         int32_t* col_idx, int64_t capacity) {
     extern __shared__ __align__(16) uint32_t smem[];
-    __shared__ uint32_t red[4];
-    uint32_t* rks = smem;
-    uint32_t* bits = smem + rks_words(p);
+    __shared__ uint32_t red[kThreads / 64];
+    uint32_t* rks = group_smem<T>(p, smem);
+    uint32_t* bits = rks + rks_words<T>(p);
     int64_t r, q; int h;
-    row_of_block(p, r, q, h);
+    if (!row_of_group(p, group_index<T>(), r, q, h)) return;      // a whole wave
     const int64_t base = row_ptr[r];
     int64_t limit = row_ptr[r + 1] - base;
     // Never write outside col_idx[0, capacity), whatever row_ptr holds.
     if (base < 0 || limit < 0 || base > capacity) return;
     if (limit > capacity - base) limit = capacity - base;
     const RowGeom g = row_geometry(p, q);
-    build_row_bitmap(p, q, h, g, rks, bits);
+    build_row_bitmap<T>(p, q, h, g, rks, bits);
     const uint32_t W = (g.pool + 31u) >> 5;
-    uint32_t c = 0;
-    for (uint32_t w = threadIdx.x; w < W; w += kThreads) c += __popc(bits[w]);
-    const int64_t count = (int64_t)block_sum(c, red) + g.clique_len;
-    emit_row(bits, W, col_idx + base, limit, g, red, count);
+    const int64_t count = (int64_t)row_popcount<T>(bits, W, red) + g.clique_len;
+    emit_row<T>(bits, W, col_idx + base, limit, g.clique_start, g.clique_len, red, count);
 }
 
 // ---------------------------------------------------------------------------
@@ -506,12 +591,12 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
 }
 
 // One-pass build (count, scan and fill fused), used when col_idx is sized from
-// the closed-form bound.  A persistent grid of workgroups takes tickets --
-// one or two consecutive rows each, in row order -- and builds each row's
+// the closed-form bound.  Workgroups take tickets -- a row or a chunk of rows
+// each, in row order -- and build each row's
 // bitmap once.  A row's offset is
 // found by a decoupled look-back over its predecessors' status words, which
-// live in row_ptr itself (the protocol and its flags are in lookback.h).  A
-// workgroup publishes a row's size as soon as its bitmap is built and keeps
+// live in row_ptr itself (the protocol and its flags are in lookback.h).  In the
+// persistent grid (k_mask_fused) a workgroup publishes a row's size as soon as its bitmap is built and keeps
 // the bitmap in LDS while it builds the next rows; it looks back for the row's
 // offset (64 predecessors per step, one per lane) and writes its keys only
 // after up to two more rows, when the predecessors, whose rows were taken
@@ -532,172 +617,282 @@ __device__ __forceinline__ void status_store(int64_t* p, int64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A row of the one-pass build whose size is published but whose keys are not
-// yet written: its bitmap waits in LDS until its offset is known.
+// A row of the persistent build whose size is published but whose keys are not
+// yet written: its bitmap waits in LDS until its offset is known, and so does
+// this (registers that hold it through the walk cost 1-2% in spills).
 struct PendingRow {
-    int64_t row;
-    int64_t count;
-    RowGeom g;
-    uint32_t* bits;
+    uint32_t row, count;         // rows and their sizes are below 2^31
+    uint32_t pool, clique_len;   // the clique, if any, starts at the pool's end
 };
 
-// Find the offset of row x.row by the decoupled look-back, publish its
-// inclusive prefix and write its keys.  Block-wide; starts and ends with every
-// thread of the block present.
+// Decoupled look-back, by one whole wave: the number of entries before unit j
+// (a row, or a chunk of rows), whose predecessors' statuses lie `stride` entries
+// of row_ptr apart (unit i's at row_ptr[(i + 1) * stride]).  Each step covers 64
+// predecessors, one per lane, and ends at the nearest one whose inclusive
+// prefix is known, once every one before it is ready.  Returns -1 when the
+// wait gave up or met poison.
+__device__ __forceinline__ int64_t look_back(const MaskParams& p, const int64_t* row_ptr, int64_t j, int stride) {
+    namespace lb = lookback;
+    const int lane = threadIdx.x & 63;
+    int64_t prefix = 0;
+    uint32_t spins = 0;
+    while (j > 0) {
+        const int64_t idx = j - lane;                       // unit idx-1's status
+        int64_t v = idx > 0 ? status_load(&row_ptr[idx * stride]) : lb::inclusive(0, false);
+        int first;
+        for (;;) {
+            const uint64_t inc = __ballot(lb::is_inclusive(v));
+            first = lb::step_end(inc, __ballot(lb::is_ready(v)));
+            if (first >= 0) break;
+            if (spins++ >= p.spin_limit) return -1;
+            __builtin_amdgcn_s_sleep(1);
+            // Only the statuses still missing, up to the nearest inclusive
+            // one, are read again: the polls' traffic slows the others.
+            if (!lb::is_ready(v) && (inc == 0 || lane < __builtin_ctzll(inc))) v = status_load(&row_ptr[idx * stride]);
+        }
+        // Lanes before `first` hold single units' counts (their sum stays below
+        // 2^32); lane `first` holds an inclusive prefix, or poison.
+        prefix += (int64_t)wave_sum_u32(lane < first ? (uint32_t)lb::value(v) : 0u);
+        if (first < 64) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, first);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), first);
+            const int64_t vf = (int64_t)(((uint64_t)hi << 32) | lo);
+            return lb::is_poisoned(vf) ? -1 : prefix + lb::value(vf);
+        }
+        j -= 64;
+    }
+    return prefix;
+}
+
+// Find the offset of row x.row, publish its inclusive prefix and write its
+// keys.  Block-wide; starts and ends with every thread of the block present.
+// x lies in LDS, written by thread 0: the first wave may read it at once, the
+// others from the barrier on.
 __device__ void resolve_and_emit(const MaskParams& p, int64_t* row_ptr, int32_t* col_idx, int64_t capacity,
-                                 const PendingRow& x, uint32_t* red, int64_t* s_base) {
+                                 const PendingRow& x, const uint32_t* bits, uint32_t* red, int64_t* s_base) {
     namespace lb = lookback;
     if (threadIdx.x < 64) {
-        // Wave-wide look-back: lane i reads the status of row j-1-i, so each
-        // step covers 64 predecessors.  The step ends at the nearest row whose
-        // inclusive prefix is known, once every row before it is ready.
-        const int lane = threadIdx.x;
-        int64_t prefix = 0;
-        bool poisoned = x.row == p.poison_row;   // test hook: as if the wait had given up
-        uint32_t spins = 0;
-        for (int64_t j = poisoned ? 0 : x.row; j > 0;) {
-            const int64_t idx = j - lane;                       // row idx-1's status
-            const int64_t v = idx > 0 ? status_load(&row_ptr[idx]) : lb::inclusive(0, false);
-            const int first = lb::step_end(__ballot(lb::is_inclusive(v)), __ballot(lb::is_ready(v)));
-            if (first < 0) {
-                if (spins++ >= p.spin_limit) { poisoned = true; break; }
-                __builtin_amdgcn_s_sleep(1);
-                continue;
-            }
-            // Lanes before `first` hold single row counts (below 2^32); lane
-            // `first` holds an inclusive prefix, or poison.
-            int64_t part = (int64_t)wave_sum_u32(lane < first ? (uint32_t)lb::value(v) : 0u);
-            if (first < 64) {
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, first);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), first);
-                const int64_t vf = (int64_t)(((uint64_t)hi << 32) | lo);
-                if (lb::is_poisoned(vf)) { poisoned = true; break; }
-                part += lb::value(vf);
-            }
-            prefix += part;
-            if (first < 64) break;
-            j -= 64;
-        }
-        if (lane == 0) {
-            status_store(&row_ptr[x.row + 1], lb::inclusive(prefix + x.count, poisoned));
-            *s_base = poisoned ? -1 : prefix;
+        const int64_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)x.row);
+        // the test hook's row: as if its wait had given up
+        const int64_t prefix = row == p.poison_row ? -1 : look_back(p, row_ptr, row, 1);
+        if (threadIdx.x == 0) {
+            status_store(&row_ptr[row + 1], lb::inclusive(prefix + (int64_t)x.count, prefix < 0));
+            *s_base = prefix;
         }
     }
     __syncthreads();
     const int64_t base = uniform_i64(*s_base);
     if (base >= 0 && base <= capacity) {
-        int64_t limit = x.count;
+        const auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+        const int64_t count = uniform(x.count);
+        int64_t limit = count;
         if (limit > capacity - base) limit = capacity - base;
-        emit_row(x.bits, (x.g.pool + 31u) >> 5, col_idx + base, limit, x.g, red, x.count);
+        const uint32_t pool = uniform(x.pool);
+        emit_row<kThreads>(bits, (pool + 31u) >> 5, col_idx + base, limit, pool, uniform(x.clique_len), red, count);
     }
 }
 
-// Persistent one-pass build.  Every workgroup takes rows (tickets of
-// kRowsPerTicket consecutive rows, in row order) until none is left.  It
+// One-pass build by chunks: a workgroup takes one ticket -- kRows consecutive
+// rows, one per group of T threads --, builds their bitmaps, publishes the
+// chunk's size, finds its offset by the look-back over the chunks before it
+// and writes the rows.  The chunk's status is the row_ptr entry of its last
+// row; the entries of its other rows are written at once as they stay.
+// With `fold` the last workgroup to finish strips the statuses (the count of
+// finished workgroups lives in the high half of row_ptr[0], the tickets in the
+// low one); otherwise the last ticket restores row_ptr[0].
+__device__ void strip_entry(int64_t* row_ptr, int64_t at, bool& poison) {
+    const int64_t v = status_load(&row_ptr[at]);
+    poison |= lookback::is_poisoned(v);
+    status_store(&row_ptr[at], lookback::stripped(v));
+}
+
+template <int T, int kRows>
+__global__ __launch_bounds__(T * kRows, 8) void k_mask_chunk(MaskParams p, int64_t* row_ptr, int32_t* col_idx,
+                                                         int64_t capacity, int fold) {
+    extern __shared__ __align__(16) uint32_t smem[];
+    __shared__ uint32_t red[T * kRows / 64], s_count[kRows];
+    __shared__ int64_t s_ticket, s_base;
+    __shared__ int s_last;
+    namespace lb = lookback;
+    const int64_t R = (int64_t)p.heads * p.nq;
+    const int grp = kRows == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / T));
+    uint32_t* rks = smem + (int64_t)grp * group_words<T>(p);
+    uint32_t* bits = rks + rks_words<T>(p);
+    if (threadIdx.x == 0) {
+        const unsigned long long t = atomicAdd(reinterpret_cast<unsigned long long*>(row_ptr), 1ull);
+        s_ticket = (int64_t)(uint32_t)t;
+        if (!fold && t == (unsigned long long)gridDim.x - 1) status_store(row_ptr, 0);
+    }
+    __syncthreads();
+    const int64_t chunk = uniform_i64(s_ticket);
+    const int64_t r0 = chunk * kRows, r = r0 + grp;
+    const int rows = (int)(R - r0 < kRows ? R - r0 : kRows);      // rows of this chunk
+    // One batch of seeds: the row words of all the chunk's (row, seed) pairs,
+    // spread over the workgroup's lanes (a row of 10 seeds alone would leave 54
+    // of its wave's 64 lanes idle through the Philox rounds).
+    const bool shared_words = T == 64 && p.n_seeds <= kSeedBatch<T>;
+    if (shared_words) {
+        for (int t = threadIdx.x; t < rows * p.n_seeds; t += T * kRows) {
+            const int i = t / p.n_seeds, sd = t - i * p.n_seeds;
+            const int h = (int)((r0 + i) / p.nq);
+            store_row_words(p, sd, p.q0 + (r0 + i - (int64_t)h * p.nq), h,
+                            smem + i * group_words<T>(p) + sd * kRowWords);
+        }
+        __syncthreads();
+    }
+    RowGeom g = {};
+    uint32_t W = 0;
+    int64_t count = 0;
+    if (grp < rows) {
+        const int h = (int)(r / p.nq);
+        const int64_t q = p.q0 + (r - (int64_t)h * p.nq);
+        g = row_geometry(p, q);
+        W = (g.pool + 31u) >> 5;
+        build_row_bitmap<T>(p, q, h, g, rks, bits, shared_words);
+        count = (int64_t)__builtin_amdgcn_readfirstlane((int)row_popcount<T>(bits, W, red)) + g.clique_len;
+        if (group_tid<T>() == 0) s_count[grp] = (uint32_t)count;
+    }
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        const uint32_t c = i < rows ? s_count[i] : 0u;
+        before += i < grp ? c : 0u;
+        total += c;
+    }
+    if (threadIdx.x < 64) {
+        int64_t* status = &row_ptr[r0 + rows];
+        if (threadIdx.x == 0) status_store(status, lb::aggregate(total));
+        const int64_t prefix = look_back(p, row_ptr, chunk, kRows);
+        // the test hook's row poisons itself and what follows
+        const bool hook = p.poison_row >= r0 && p.poison_row < r0 + rows;
+        if (threadIdx.x == 0) {
+            status_store(status, lb::inclusive(prefix + total, prefix < 0 || hook));
+            s_base = prefix;
+        }
+    }
+    __syncthreads();
+    const int64_t first = uniform_i64(s_base);
+    const bool bad = first < 0 || (p.poison_row >= r0 && p.poison_row <= r);
+    if (grp < rows) {
+        const int64_t base = first + before;
+        if (group_tid<T>() == 0 && grp + 1 < rows) status_store(&row_ptr[r + 1], bad ? -1 : base + count);
+        if (!bad && base <= capacity) {
+            int64_t limit = count;
+            if (limit > capacity - base) limit = capacity - base;
+            emit_row<T>(bits, W, col_idx + base, limit, g.clique_start, g.clique_len, red, count);
+        }
+    }
+    if (!fold) return;
+    if (threadIdx.x == 0) {
+        // this thread wrote the chunk's status (through to memory): done before the count
+        __builtin_amdgcn_s_waitcnt(0);
+        const uint64_t old = __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(row_ptr), 1ull << 32,
+                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = (old >> 32) == (uint64_t)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;                                      // the same in every thread
+    bool poison = false;
+    for (int64_t c = threadIdx.x; c < (int64_t)gridDim.x; c += T * kRows)
+        strip_entry(row_ptr, (c + 1) * kRows < R ? (c + 1) * kRows : R, poison);
+    const int any = __syncthreads_or(poison);
+    if (threadIdx.x == 0) {
+        if (any) status_store(&row_ptr[R], -1);
+        status_store(row_ptr, 0);
+    }
+}
+
+// Persistent one-pass build.  Every workgroup takes rows (a ticket each,
+// in row order) until none is left.  It
 // publishes a row's size as soon as the row's
 // bitmap is built, but looks back for the row's offset only after building
 // kDepth more rows: by then its predecessors have almost always published
 // their sizes, so the look-back rarely waits (kDepth = 0: at once).
 // kDepth + 1 bitmaps per workgroup rotate through the rows.
-template <int kDepth, int kRowsPerTicket>
+template <int kDepth>
 __global__ __launch_bounds__(kThreads, kDepth == 2 ? 6 : 8) void k_mask_fused(MaskParams p, int64_t* row_ptr,
                                                                              int32_t* col_idx, int64_t capacity) {
     static_assert(kDepth >= 0 && kDepth <= 2, "at most two rows wait for their offsets");
     extern __shared__ __align__(16) uint32_t smem[];
-    __shared__ uint32_t red[4];
-    __shared__ int64_t s_ticket, s_base;
+    __shared__ int64_t s_ticket;
+    __shared__ PendingRow ring[kDepth + 1];
     namespace lb = lookback;
-    uint32_t* rks = smem;
-    uint32_t* bitmaps = smem + rks_words(p);
-    const int64_t bw = bitmap_words(p);
+    // The row words are dead between a walk and the next row's: the reductions'
+    // and the offset's words live there (a few bytes more of LDS cost the 64k
+    // layer's sixth workgroup per CU, and 3.5% of the build).
+    uint32_t* red = smem;
+    int64_t* s_base = reinterpret_cast<int64_t*>(smem + kThreads / 64);
+    static_assert(kThreads / 64 + 2 <= kRowWords, "one seed's row words hold both");
+    const uint32_t first_at = (uint32_t)rks_words<kThreads>(p), bw = (uint32_t)bitmap_words(p);
     const int64_t R = (int64_t)p.heads * p.nq;
-    PendingRow q0 = {}, q1 = {};
-    int n = 0;
-    // Tickets that carry rows; every workgroup takes tickets until one is
-    // past them, so T + gridDim.x tickets are taken in all, and the last one
-    // restores row_ptr[0] to 0.
-    const int64_t T = (R + kRowsPerTicket - 1) / kRowsPerTicket;
-    // With two rows per ticket, s_next holds the pair's second row until its
-    // turn (R when there is none); thread 0 alone uses it, and it lives in LDS
-    // so that no register holds it through the walk.
-    __shared__ int64_t s_next;
-    if (kRowsPerTicket > 1 && threadIdx.x == 0) s_next = R;
-    for (int it = 0;; ++it) {
-        if (threadIdx.x == 0) {
-            if constexpr (kRowsPerTicket == 1) {
-                const int64_t t = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(row_ptr), 1ull);
-                s_ticket = t;
-                if (t == T + (int64_t)gridDim.x - 1) status_store(row_ptr, 0);
-            } else if (s_next >= R) {
-                const int64_t t = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(row_ptr), 1ull);
-                if (t == T + (int64_t)gridDim.x - 1) status_store(row_ptr, 0);
-                const int64_t first = t < T ? t * kRowsPerTicket : R;
-                s_ticket = first;
-                s_next = first + 1 < R ? first + 1 : R;
-            } else {
-                s_ticket = s_next;
-                s_next = R;
+    int waiting = 0, in = 0, out = 0;      // rows that wait; the ring's next entry to fill and to resolve
+    bool more = true;
+    for (;;) {
+        // Every workgroup takes tickets until one is past the rows, so R +
+        // gridDim.x are taken in all, and the last one restores row_ptr[0] to 0.
+        if (more && threadIdx.x == 0) {
+            const int64_t t = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(row_ptr), 1ull);
+            s_ticket = t;
+            if (t == R + (int64_t)gridDim.x - 1) status_store(row_ptr, 0);
+        }
+        __syncthreads();   // also: last iteration's bitmap, offset and ring entry are no longer read
+        if (more) {
+            const int64_t r = uniform_i64(s_ticket);
+            more = r < R;
+            if (more) {
+                const int h = (int)(r / p.nq);
+                const int64_t q = p.q0 + (r - (int64_t)h * p.nq);
+                const RowGeom g = row_geometry(p, q);
+                const uint32_t at = first_at + in * bw;
+                build_row_bitmap<kThreads>(p, q, h, g, smem, smem + at);
+                const uint32_t W = (g.pool + 31u) >> 5;
+                const uint32_t count = row_popcount<kThreads>(smem + at, W, red) + g.clique_len;
+                if (threadIdx.x == 0) {
+                    status_store(&row_ptr[r + 1], lb::aggregate(count));
+                    ring[in] = {(uint32_t)r, count, g.pool, g.clique_len};
+                }
+                in = in == kDepth ? 0 : in + 1;
+                ++waiting;
             }
         }
-        __syncthreads();   // also: the bitmap emitted last iteration is no longer read
-        const int64_t r = uniform_i64(s_ticket);
-        if (r >= R) {
-            if (kDepth > 0 && n > 0) resolve_and_emit(p, row_ptr, col_idx, capacity, q0, red, &s_base);
-            if (kDepth > 1 && n > 1) resolve_and_emit(p, row_ptr, col_idx, capacity, q1, red, &s_base);
+        if (waiting > (more ? kDepth : 0)) {
+            resolve_and_emit(p, row_ptr, col_idx, capacity, ring[out], smem + first_at + out * bw, red, s_base);
+            out = out == kDepth ? 0 : out + 1;
+            --waiting;
+        } else if (!more) {
             break;
         }
-        PendingRow fresh;
-        fresh.row = r;
-        fresh.bits = bitmaps + (int64_t)(it % (kDepth + 1)) * bw;
-        {
-            const int h = (int)(r / p.nq);
-            const int64_t q = p.q0 + (r - (int64_t)h * p.nq);
-            fresh.g = row_geometry(p, q);
-            build_row_bitmap(p, q, h, fresh.g, rks, fresh.bits);
-            const uint32_t W = (fresh.g.pool + 31u) >> 5;
-            uint32_t c = 0;
-            for (uint32_t w = threadIdx.x; w < W; w += kThreads) c += __popc(fresh.bits[w]);
-            fresh.count = (int64_t)__builtin_amdgcn_readfirstlane((int)block_sum(c, red)) + fresh.g.clique_len;
-            if (threadIdx.x == 0) status_store(&row_ptr[r + 1], lb::aggregate(fresh.count));
-        }
-        if (kDepth == 0) {
-            resolve_and_emit(p, row_ptr, col_idx, capacity, fresh, red, &s_base);
-            continue;
-        }
-        if (n == kDepth) {
-            resolve_and_emit(p, row_ptr, col_idx, capacity, q0, red, &s_base);
-            if (kDepth > 1) q0 = q1;
-            --n;
-        }
-        if (n == 0) q0 = fresh;
-        else q1 = fresh;
-        ++n;
     }
 }
 
-__global__ void k_fill_i64(int64_t* x, int64_t n, int64_t v) {
+// Clear row_ptr[0] and the status entries of `units` units of `stride` rows each.
+__global__ void k_clear_status(int64_t* row_ptr, int64_t R, int64_t units, int stride) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = v;
+    if (i <= units) row_ptr[i * stride < R ? i * stride : R] = 0;
 }
 
-// After the one-pass build: strip the status flags of row_ptr[1 .. R].  A
-// poisoned row's entry becomes -1; if any row is poisoned, row_ptr[R] becomes
-// -1 as well.  row_ptr[0] is 0 when this runs (the fused kernel's last ticket
-// restores it); here it counts finished workgroups (low 32 bits) and poisoned
+// After the one-pass build: strip the flags of the units' status entries.  A
+// poisoned entry becomes -1; if any is poisoned, row_ptr[R] becomes
+// -1 as well.  row_ptr[0] is 0 when this runs (the last ticket restores it);
+// here it counts finished workgroups (low 32 bits) and poisoned
 // ones (high bits), and the last workgroup to finish resets it to 0.
-__global__ __launch_bounds__(256) void k_strip_status(int64_t* row_ptr, int64_t R) {
+__global__ __launch_bounds__(256) void k_strip_status(int64_t* row_ptr, int64_t R, int64_t units, int stride) {
     const int64_t i = 1 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool poison = false;
-    if (i <= R) {
-        const int64_t v = row_ptr[i];
+    if (i <= units) {
+        const int64_t at = i * stride < R ? i * stride : R;
+        const int64_t v = row_ptr[at];
         poison = lookback::is_poisoned(v);
-        row_ptr[i] = lookback::stripped(v);
+        // through to memory, and done before the count below: the total's -1 must be the last write
+        status_store(&row_ptr[at], lookback::stripped(v));
+        __builtin_amdgcn_s_waitcnt(0);
     }
     const int any = __syncthreads_or(poison);
     if (threadIdx.x == 0) {
         const uint64_t add = 1ull | (any ? (1ull << 32) : 0ull);
         const uint64_t old = __hip_atomic_fetch_add(reinterpret_cast<uint64_t*>(row_ptr), add,
-                                                    __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((old & 0xFFFFFFFFull) == (uint64_t)gridDim.x - 1) {
             // every other workgroup has stripped its entries
             if (((old + add) >> 32) != 0) status_store(&row_ptr[R], -1);
@@ -751,28 +946,101 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_rows(int64_t* row_ptr, in
 }
 
 size_t mask_smem_bytes(const MaskParams& p, int bitmaps = 1) {
-    return (size_t)(rks_words(p) + bitmaps * bitmap_words(p)) * sizeof(uint32_t);
+    return (size_t)(rks_words<kThreads>(p) + bitmaps * bitmap_words(p)) * sizeof(uint32_t);
+}
+// `groups` groups of T threads, one row each.
+template <int T>
+size_t group_smem_bytes(const MaskParams& p, int groups) {
+    return (size_t)(groups * group_words<T>(p)) * sizeof(uint32_t);
 }
 
 // Workgroups per CU below which a deeper one-pass pipeline costs more
 // occupancy than its shorter waits gain.
 constexpr int kMinResidentRows = 6;
-// Expected draws per row below which the one-pass build takes two rows per
-// ticket (measured crossover on MI355X between 4,900 and 6,600).
-constexpr int64_t kTicketPairDraws = 5000;
+// Rows of fewer expected draws are built by a wave each.  A workgroup to such a
+// row spends most of its time between barriers and takes a ticket per row
+// (12.5 ns each on MI355X, whatever the row's work): 32k layers of 10 seeds
+// (1,640 draws) 608 -> 340 us, an 8k layer of 70 (2,870) 211 -> 170, a 4k layer
+// of 10 90 -> 34; 4,900 draws 949 -> 702, 6,600 2,188 -> 1,932, 9,800 2,735 ->
+// 2,660.  From there the LDS of a bitmap per wave leaves too few waves (11,500
+// draws 1,537 -> 1,548, 23,000 4,980 -> 5,550).
+constexpr int64_t kWaveDraws = 9000;
+// Rows (waves) per workgroup: 8 up to this many draws, where fewer, larger
+// chunks shorten the look-back (4k layer 34 against 45 us with 4), 4 above (a
+// chunk waits for its slowest row: 6,600 draws 1,932 against 2,021 with 8) and
+// where eight bitmaps would leave one workgroup to a CU (100,000 keys: 1,106
+// against 1,550 us).
+constexpr int64_t kChunk8Draws = 4000;
+constexpr size_t kChunk8Smem = 80 << 10;
+// Pools of 160,000 keys and more (four bitmaps over 80 KB, one workgroup of four
+// waves to a CU) go to the persistent grid: 262,144 keys, 6,600 draws 8.0
+// against 13.6 ms.  The two-phase build's waves end earlier: 100,000 keys 1.94
+// against 2.07 ms, 150,000 4.36 against 3.39.
+constexpr size_t kWaveSmem = 80 << 10;
+constexpr size_t kWaveSmemTwoPhase = 64 << 10;
+// Builds of at most this many rows leave CUs idle with 256 lanes to a row; 1,024
+// lanes take a row of 46,000 draws in 29 instead of 47 us (2 rows; 512 rows of
+// the same 63 instead of 75, 1,024 rows 109 against 105), and one of 655 in 13
+// instead of 22 (a wave: 19).  Rows of a few draws a lane stay with the waves.
+constexpr int64_t kFewRows = 512;
+constexpr int64_t kFewRowsDraws = 256;
 
 template <int kDepth>
 hipError_t fused_occupancy(const MaskParams& p, int* blocks) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_mask_fused<kDepth, 1>, kThreads,
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_mask_fused<kDepth>, kThreads,
                                                         mask_smem_bytes(p, kDepth + 1));
+}
+
+// Expected draws of the middle row.
+int64_t middle_draws(const MaskParams& p) {
+    const int64_t mid = p.q0 + p.nq / 2;
+    return (int64_t)p.n_seeds * row_count(p.ppm, p.causal ? mid + 1 : p.N);
+}
+
+hipError_t clear_status(int64_t* row_ptr, int64_t rows, int64_t units, int stride, hipStream_t st) {
+    hipLaunchKernelGGL(k_clear_status, dim3((unsigned)((units + 1 + 255) / 256)), dim3(256), 0, st, row_ptr, rows,
+                       units, stride);
+    return hipGetLastError();
+}
+hipError_t strip_status(int64_t* row_ptr, int64_t rows, int64_t units, int stride, hipStream_t st) {
+    hipLaunchKernelGGL(k_strip_status, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, st, row_ptr, rows, units,
+                       stride);
+    return hipGetLastError();
+}
+
+// Chunks up to which the build's last workgroup strips the statuses itself.
+constexpr int64_t kFoldChunks = 1024;
+
+template <int T, int kRows>
+hipError_t run_mask_chunk(const MaskParams& p, int64_t* row_ptr, int32_t* col_idx, int64_t capacity, hipStream_t st) {
+    const int64_t rows = (int64_t)p.heads * p.nq, chunks = (rows + kRows - 1) / kRows;
+    hipError_t e = clear_status(row_ptr, rows, chunks, kRows, st);
+    if (e != hipSuccess) return e;
+    const int fold = chunks <= kFoldChunks;
+    hipLaunchKernelGGL((k_mask_chunk<T, kRows>), dim3((unsigned)chunks), dim3(T * kRows),
+                       group_smem_bytes<T>(p, kRows), st, p, row_ptr, col_idx, capacity, fold);
+    e = hipGetLastError();
+    if (e != hipSuccess || fold) return e;
+    return strip_status(row_ptr, rows, chunks, kRows, st);
+}
+
+// Two-phase build: waves for light rows.
+bool two_phase_waves(const MaskParams& p) {
+    return middle_draws(p) < kWaveDraws && group_smem_bytes<64>(p, kThreads / 64) <= kWaveSmemTwoPhase;
 }
 
 }  // namespace
 
 hipError_t launch_mask_count(const MaskParams& p, int64_t* row_ptr, hipStream_t st) {
     const int64_t rows = (int64_t)p.heads * p.nq;
-    hipLaunchKernelGGL(k_mask_count, dim3((unsigned)rows), dim3(kThreads), mask_smem_bytes(p), st, p,
-                       row_ptr);
+    if (two_phase_waves(p)) {
+        constexpr int kRows = kThreads / 64;
+        hipLaunchKernelGGL(k_mask_count<64>, dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(kThreads),
+                           group_smem_bytes<64>(p, kRows), st, p, row_ptr);
+    } else {
+        hipLaunchKernelGGL(k_mask_count<kThreads>, dim3((unsigned)rows), dim3(kThreads), mask_smem_bytes(p), st, p,
+                           row_ptr);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_scan_rows, dim3(1), dim3(kScanThreads), 0, st, row_ptr, rows);
@@ -781,10 +1049,15 @@ hipError_t launch_mask_count(const MaskParams& p, int64_t* row_ptr, hipStream_t 
 
 hipError_t launch_mask_fused(const MaskParams& p, int64_t* row_ptr, int32_t* col_idx,
                              int64_t capacity, hipStream_t st) {
-    const int64_t rows = (int64_t)p.heads * p.nq;
-    const unsigned eb = (unsigned)((rows + 1 + 255) / 256);
-    hipLaunchKernelGGL(k_fill_i64, dim3(eb), dim3(256), 0, st, row_ptr, rows + 1, (int64_t)0);
-    hipError_t e = hipGetLastError();
+    const int64_t rows = (int64_t)p.heads * p.nq, draws = middle_draws(p);
+    if (rows <= kFewRows && draws >= kFewRowsDraws)
+        return run_mask_chunk<1024, 1>(p, row_ptr, col_idx, capacity, st);
+    if (draws < kWaveDraws && group_smem_bytes<64>(p, 4) <= kWaveSmem) {
+        if (draws < kChunk8Draws && group_smem_bytes<64>(p, 8) <= kChunk8Smem)
+            return run_mask_chunk<64, 8>(p, row_ptr, col_idx, capacity, st);
+        return run_mask_chunk<64, 4>(p, row_ptr, col_idx, capacity, st);
+    }
+    hipError_t e = clear_status(row_ptr, rows, rows, 1, st);
     if (e != hipSuccess) return e;
     // Persistent: as many workgroups as fit on the device at once, each
     // taking rows until none is left.
@@ -804,43 +1077,29 @@ hipError_t launch_mask_fused(const MaskParams& p, int64_t* row_ptr, int32_t* col
             break;
         }
     }
-    // Rows per ticket.  One same-address atomic per row caps the build at a
-    // row per ~12.5 ns on MI355X whatever the row's work; light rows (expected
-    // draws per row, seeds x k at the middle row, below kTicketPairDraws)
-    // take two consecutive rows per ticket, which halves that floor.  Heavier
-    // rows keep one: a pair's second row publishes its size an iteration
-    // later, and the look-backs behind it wait (measured: 32k layer with 10
-    // seeds 0.84 -> 0.63 ms with pairs, 64k with 70 seeds 4.93 -> 5.47 ms).
-    const int64_t mid = p.q0 + p.nq / 2;
-    const int64_t work = (int64_t)p.n_seeds * row_count(p.ppm, p.causal ? mid + 1 : p.N);
-    const bool pairs = work < kTicketPairDraws;
-    const int64_t tickets = pairs ? (rows + 1) / 2 : rows;
     int64_t grid = (int64_t)(per_cu > 0 ? per_cu : 1) * (cus > 0 ? cus : 1);
-    if (grid > tickets) grid = tickets;
+    if (grid > rows) grid = rows;
     const size_t smem = mask_smem_bytes(p, depth + 1);
     const dim3 g3((unsigned)grid), b3(kThreads);
-    if (depth == 2) {
-        if (pairs) hipLaunchKernelGGL((k_mask_fused<2, 2>), g3, b3, smem, st, p, row_ptr, col_idx, capacity);
-        else hipLaunchKernelGGL((k_mask_fused<2, 1>), g3, b3, smem, st, p, row_ptr, col_idx, capacity);
-    } else if (depth == 1) {
-        if (pairs) hipLaunchKernelGGL((k_mask_fused<1, 2>), g3, b3, smem, st, p, row_ptr, col_idx, capacity);
-        else hipLaunchKernelGGL((k_mask_fused<1, 1>), g3, b3, smem, st, p, row_ptr, col_idx, capacity);
-    } else {
-        if (pairs) hipLaunchKernelGGL((k_mask_fused<0, 2>), g3, b3, smem, st, p, row_ptr, col_idx, capacity);
-        else hipLaunchKernelGGL((k_mask_fused<0, 1>), g3, b3, smem, st, p, row_ptr, col_idx, capacity);
-    }
+    if (depth == 2) hipLaunchKernelGGL(k_mask_fused<2>, g3, b3, smem, st, p, row_ptr, col_idx, capacity);
+    else if (depth == 1) hipLaunchKernelGGL(k_mask_fused<1>, g3, b3, smem, st, p, row_ptr, col_idx, capacity);
+    else hipLaunchKernelGGL(k_mask_fused<0>, g3, b3, smem, st, p, row_ptr, col_idx, capacity);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned sb = (unsigned)((rows + 255) / 256);
-    hipLaunchKernelGGL(k_strip_status, dim3(sb), dim3(256), 0, st, row_ptr, rows);
-    return hipGetLastError();
+    return strip_status(row_ptr, rows, rows, 1, st);
 }
 
 hipError_t launch_mask_fill(const MaskParams& p, const int64_t* row_ptr, int32_t* col_idx,
                             int64_t capacity, hipStream_t st) {
     const int64_t rows = (int64_t)p.heads * p.nq;
-    hipLaunchKernelGGL(k_mask_fill, dim3((unsigned)rows), dim3(kThreads), mask_smem_bytes(p), st, p,
-                       row_ptr, col_idx, capacity);
+    if (two_phase_waves(p)) {
+        constexpr int kRows = kThreads / 64;
+        hipLaunchKernelGGL(k_mask_fill<64>, dim3((unsigned)((rows + kRows - 1) / kRows)), dim3(kThreads),
+                           group_smem_bytes<64>(p, kRows), st, p, row_ptr, col_idx, capacity);
+    } else {
+        hipLaunchKernelGGL(k_mask_fill<kThreads>, dim3((unsigned)rows), dim3(kThreads), mask_smem_bytes(p), st, p,
+                           row_ptr, col_idx, capacity);
+    }
     return hipGetLastError();
 }
 

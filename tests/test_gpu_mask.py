@@ -248,3 +248,40 @@ def test_forced_poison_row_is_reported(monkeypatch):
     rp_h, poisoned = _give_up_case(ris, monkeypatch, "RIS_DEBUG_POISON_ROW", r, must_poison=True)
     assert rp_h[r + 1] == -1 and r in poisoned
     assert (rp_h[1:r + 1] >= 0).all(), "a row before the poisoned one was poisoned"
+
+
+# One row range per form of the builds, at its edges (draws: of the middle row).
+DISPATCH = [
+    # mode, ppm, N, heads, S, block, window, anchor, q_begin, q_count
+    (0, 10_000, 4097, 2, 70, 0, 0, 0, 3841, 256),       # 512 rows, 2,800 draws: 1,024 lanes to a row
+    (0, 10_000, 4097, 2, 70, 0, 0, 0, 3840, 257),       # 514 rows: 8 waves, a last chunk of two rows
+    (0, 100_000, 512, 1, 4, 0, 0, 0, 0, 512),           # 512 rows, 104 draws: 8 waves
+    (1, 50_000, 2000, 1, 100, 64, 33, 4, 0, 2000),      # two seed batches of 50 to a wave, 8 waves
+    (0, 50_000, 2001, 1, 100, 0, 0, 0, 0, 2001),        # 5,000 draws: 4 waves, a last chunk of one row
+    (0, 100_000, 1500, 1, 130, 0, 0, 0, 0, 1500),       # 9,750 draws: the persistent grid, two rows in flight
+    (0, 1_000, 80000, 1, 125, 0, 0, 0, 79400, 600),     # 10,000 draws, 80,000 keys: one row in flight
+    (0, 1_000, 150000, 1, 65, 0, 0, 0, 149400, 600),    # 9,750 draws, 150,000 keys: none in flight
+    (0, 1_000, 262144, 1, 2, 0, 0, 0, 261544, 600),     # light rows whose bitmaps are too large for waves
+]
+
+
+@pytest.mark.parametrize("fused", [False, True], ids=["two_phase", "one_pass"])
+@pytest.mark.parametrize("case", DISPATCH)
+def test_mask_rows_at_dispatch_edges(case, fused):
+    """Each form builds the definition's rows, and writes nothing beyond them."""
+    ris = need_gpu()
+    mode, ppm, N, heads, S, block, window, anchor, q0, nq = case
+    sp = spec_of(mode, ppm, N, heads, S, 3, 2, 1, block, window, anchor)
+    say(f"mask rows {case} fused={fused}")
+    d = desc_of(ris, sp)
+    rp = torch.full((heads * nq + 1,), -7, dtype=torch.int64, device="cuda")
+    if not fused:
+        ris.mask_build_rows(d, q0, nq, rp)
+    cap = ris.mask_rows_nnz_bound(d, q0, nq) if fused else int(rp[-1].item())
+    ci = torch.full((cap + 8,), -9, dtype=torch.int32, device="cuda")
+    ris.mask_build_rows(d, q0, nq, rp, ci, col_capacity=cap)
+    rp_h, ci_h = rp.cpu().numpy(), ci.cpu().numpy()
+    want = [w for h in range(heads) for w in o_geo.row_sets(sp, h, np.arange(q0, q0 + nq))]
+    assert np.array_equal(rp_h, np.concatenate([[0], np.cumsum([len(w) for w in want])]))
+    assert np.array_equal(ci_h[:rp_h[-1]], np.concatenate(want))
+    assert (ci_h[rp_h[-1]:] == -9).all()
