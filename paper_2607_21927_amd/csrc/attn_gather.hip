@@ -1,25 +1,15 @@
 // Sparse attention, gather form: one wavefront per (kv_head g, query row q),
 // for the 32-row tiles whose union density leaves the tiled kernel idle.
 //
-// bf16 inputs (k_attn_gather16): the matrix unit does both products.  The
-// row's unified index set I(g, q) (CSR) is walked in 32-key tiles; each key
-// row of K and V is gathered once for all G query heads of the group (the
-// heads are the 16-wide MFMA dimension), one online softmax per head runs
-// over the whole set, and the next tile's rows are loaded while the current
-// one is computed.  Every index of the set enters the single normalisation
-// once (Pre-Fusion Unified Softmax; Methods, "Hybrid Anchor and Pre-Fusion
-// Unified Softmax").
+// The matrix unit does both products.  The row's unified index set I(g, q) (CSR)
+// is walked in tiles of keys; each key row of K and V is gathered once for all G
+// query heads of the group (the heads are the 16-wide MFMA dimension), one
+// online softmax per head runs over the whole set, and the next tile's rows are
+// loaded while the current one is computed.  Every index of the set enters the
+// single normalisation once (Pre-Fusion Unified Softmax; Methods, "Hybrid
+// Anchor and Pre-Fusion Unified Softmax").  bf16 inputs run on k_attn_gather16,
+// float32 ones on k_attn_gather.
 //
-// float32 inputs (k_attn_gather): vector-unit form.  Chunks of 64 keys:
-//   1. scores  -- lane l owns key j_l of the chunk, reads K[g, j_l] once and
-//      forms <Q[h, q], K[g, j_l]> for every query head h of the GQA group
-//      (the G query rows sit in LDS and are read as broadcasts);
-//   2. softmax -- one running (max, sum) per head over the whole set:
-//      wavefront max and sum by DPP, rescale of the accumulators when the
-//      max grows;
-//   3. PV      -- lanes switch to owning D/64 consecutive dimensions; for each
-//      key of the chunk the wave reads the value row as one contiguous
-//      segment and accumulates p_h * V for all G heads.
 // Scores are kept in the log2 domain (scale * log2(e) folded in) so the
 // exponentials are exp2.  Rows are launched in descending q: the heavy rows
 // start first.
@@ -29,200 +19,198 @@
 namespace ris {
 namespace {
 
-constexpr int kGMax = 8;
-
-template <bool BF16>
-__device__ __forceinline__ float load_elem(const void* base, int64_t idx) {
-    if constexpr (BF16) return bf16_to_f32(static_cast<const uint16_t*>(base)[idx]);
-    else return static_cast<const float*>(base)[idx];
-}
-
-// Unpack one 16-byte vector of inputs into floats.
-template <bool BF16>
-__device__ __forceinline__ void unpack16(const uint4& u, float* f) {
-    if constexpr (BF16) {
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            f[2 * e] = __uint_as_float(w[e] << 16);
-            f[2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
-        }
-    } else {
-        f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y);
-        f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
-    }
-}
-
-// DPL consecutive elements of a row starting at element `off`.
-template <bool BF16, int DPL>
-__device__ __forceinline__ void load_dims(const void* base, int64_t off, float* v) {
-    if constexpr (BF16) {
-        const uint16_t* p = static_cast<const uint16_t*>(base) + off;
-        if constexpr (DPL == 2) {
-            const uint32_t w = *reinterpret_cast<const uint32_t*>(p);
-            v[0] = __uint_as_float(w << 16);
-            v[1] = __uint_as_float(w & 0xFFFF0000u);
-        } else {
-            v[0] = bf16_to_f32(p[0]);
-        }
-    } else {
-        const float* p = static_cast<const float*>(base) + off;
-        if constexpr (DPL == 2) {
-            const float2 w = *reinterpret_cast<const float2*>(p);
-            v[0] = w.x; v[1] = w.y;
-        } else {
-            v[0] = p[0];
-        }
-    }
-}
+// ---------------------------------------------------------------------------
+// float32 gather on the matrix unit: one wavefront per (kv_head g, query row
+// q), four rows per workgroup, no LDS.  The row's set is walked in tiles of
+// 16 keys at D = 128 and 32 at D = 64 (32 registers each of K and of V):
+//   * S^T = K Q^T on MFMA 16x16x4 f32 with the G query heads of the group as
+//     the 16-wide dimension; lane l loads key l%16's dims 16 s + 4 (l/16) ..
+//     as one 16-byte vector and product e of a slice takes element e of it, so
+//     both operands come straight from memory in that order of the dims;
+//   * one online softmax per head (lane l owns head l%16);
+//   * O += P V on the same MFMA: product i of a 16-key half takes the keys
+//     4 (l/16) + i, whose weights lane l holds already, and lane l loads those
+//     rows' dims 64 x + 4 (l%16) .. , whole rows over 16 lanes.
+// The next tile's K rows are loaded once the scores are formed, its V rows once
+// the outputs are.  Bound by the gathers (the matrix unit is busy about 40%, its
+// 16 columns filled by G heads).  12/2 heads, D = 128, N = 4,096, 10 seeds at
+// 1%: 363 us with a lane to a key (K rows read 16 bytes per lane and load,
+// scores and outputs on the vector unit), 205 us here: 8 TB/s of K and V rows.
+// An XCD's workgroups kept to one head's rows (its L2 then holds that head's K
+// and V) measured the same.
+// ---------------------------------------------------------------------------
+constexpr int kFWaves = 4;            // rows (waves) per workgroup
 
 template <int D>
-__global__ __launch_bounds__(64) void k_attn_gather(AttnParams a, float qscale) {
-    constexpr bool BF16 = false;                      // float32 inputs (bf16 runs on k_attn_gather16)
-    constexpr int DPL = D / 64;                       // dims per lane in PV
-    constexpr int VEC = BF16 ? 8 : 4;                 // elements per 16-byte load
-    constexpr int NV = D / VEC;
-    __shared__ __align__(16) float qs[kGMax][D];
-    __shared__ __align__(16) float ps[64][kGMax];
-
-    const int lane = threadIdx.x;
-    const int G = a.G;
+__global__ __launch_bounds__(64 * kFWaves, 3) void k_attn_gather(AttnParams a, float qscale) {
+    constexpr int KB = 128 / D;        // 16-key halves of a tile
+    constexpr int SL = D / 16;         // 16-dim slices of the score product
+    constexpr int DX = D / 64;         // 64-dim pieces of the output
+    const int lane = threadIdx.x & 63;
+    const int li = lane & 15, lg = lane >> 4;
     const int64_t N = a.N;
-    const int64_t i = blockIdx.x;
-    const int64_t q = N - 1 - i / a.Hkv;
-    const int g = (int)(i % a.Hkv);
+    const int64_t f = (int64_t)blockIdx.x * kFWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (f >= (int64_t)a.Hkv * N) return;
+    const int64_t q = N - 1 - f / a.Hkv;              // heavy rows first
+    const int g = (int)(f % a.Hkv);
     if (tile_is_dense(a, g, q - q % kTileRows)) return;   // that tile runs on the tiled kernel
-    const int64_t r = (int64_t)g * N + q;
-    int64_t start = a.row_ptr[r];
-    int64_t L = a.row_ptr[r + 1] - start;
+    const int G = a.G;
+    int64_t start = a.row_ptr[(int64_t)g * N + q];
+    int64_t L = a.row_ptr[(int64_t)g * N + q + 1] - start;
     if (start < 0 || L < 0) { start = 0; L = 0; }   // an incomplete build's rows: empty
+    const int32_t* idx = a.col_idx + start;
+    const float* Kg = static_cast<const float*>(a.K) + (int64_t)g * N * D;
+    const float* Vg = static_cast<const float*>(a.V) + (int64_t)g * N * D;
 
-    for (int e = lane; e < G * D; e += 64) {
-        const int hh = e / D, d = e - hh * D;
-        qs[hh][d] = load_elem<BF16>(a.Q, ((int64_t)(g * G + hh) * N + q) * D + d) * qscale;
+    f32x4_t qf[SL];                    // head l%16, dims 16 s + 4 (l/16) ..
+    {
+        const bool hv = li < G;
+        const float* qp = static_cast<const float*>(a.Q) + ((int64_t)(g * G + (hv ? li : 0)) * N + q) * D + 4 * lg;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(qp + 16 * s);
+            qf[s] = hv ? v * qscale : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
     }
-    __syncthreads();
+    f32x4_t o[4 * DX];                 // o[4 x + e][i]: head 4 (l/16) + i, dim 64 x + 4 (l%16) + e
+#pragma unroll
+    for (int x = 0; x < 4 * DX; ++x) o[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
 
-    float m[kGMax], l[kGMax], acc[kGMax][DPL];
+    f32x4_t kr[KB][SL], vr[KB][4][DX];
+    int jn[KB];                        // the loaded keys (slot 16 kb + l%16); -1: none
+    auto load_keys = [&](int64_t v0) {
 #pragma unroll
-    for (int hh = 0; hh < kGMax; ++hh) {
-        m[hh] = -INFINITY; l[hh] = 0.f;
+        for (int kb = 0; kb < KB; ++kb) {
+            const int64_t v = v0 + 16 * kb + li;
+            const int j = v < L ? idx[v] : -1;
+            jn[kb] = (uint32_t)j < (uint32_t)N ? j : -1;   // an index outside [0, N) is ignored
+        }
+    };
+    auto load_k = [&]() {
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) acc[hh][e] = 0.f;
-    }
-
-    const char* Kbase = static_cast<const char*>(a.K) + (int64_t)g * N * D * (BF16 ? 2 : 4);
-    const char* Vbase = static_cast<const char*>(a.V) + (int64_t)g * N * D * (BF16 ? 2 : 4);
-
-    for (int64_t c0 = 0; c0 < L; c0 += 64) {
-        const int cnt = (int)(L - c0 < 64 ? L - c0 : 64);
-        int j = lane < cnt ? a.col_idx[start + c0 + lane] : 0;
-        // An index outside [0, N) is ignored (masked) rather than dereferenced.
-        const bool valid = lane < cnt && (uint32_t)j < (uint32_t)N;
-        if (!valid) j = 0;
-
-        // ---- scores for all G heads from one read of K[g, j]
-        const uint4* krow = reinterpret_cast<const uint4*>(Kbase + (int64_t)j * D * (BF16 ? 2 : 4));
-        uint4 kraw[NV];
+        for (int kb = 0; kb < KB; ++kb) {
+            const float* kp = Kg + (int64_t)(jn[kb] < 0 ? 0 : jn[kb]) * D + 4 * lg;   // row 0 always exists
 #pragma unroll
-        for (int v = 0; v < NV; ++v) kraw[v] = krow[v];
-        float s[kGMax];
+            for (int s = 0; s < SL; ++s) kr[kb][s] = *reinterpret_cast<const f32x4_t*>(kp + 16 * s);
+        }
+    };
+    auto load_v = [&](const int (&j)[KB]) {
 #pragma unroll
-        for (int hh = 0; hh < kGMax; ++hh) s[hh] = 0.f;
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            float kf[VEC];
-            unpack16<BF16>(kraw[v], kf);
+            for (int i = 0; i < 4; ++i) {
+                const int jv = __shfl(j[kb], 4 * lg + i);
+                const float* vp = Vg + (int64_t)(jv < 0 ? 0 : jv) * D + 4 * li;
 #pragma unroll
-            for (int hh = 0; hh < kGMax; ++hh) {
-                if (hh < G) {
-                    const float4* qv = reinterpret_cast<const float4*>(&qs[hh][v * VEC]);
-#pragma unroll
-                    for (int e4 = 0; e4 < VEC / 4; ++e4) {
-                        const float4 qq = qv[e4];
-                        s[hh] = fmaf(qq.x, kf[4 * e4 + 0], s[hh]);
-                        s[hh] = fmaf(qq.y, kf[4 * e4 + 1], s[hh]);
-                        s[hh] = fmaf(qq.z, kf[4 * e4 + 2], s[hh]);
-                        s[hh] = fmaf(qq.w, kf[4 * e4 + 3], s[hh]);
-                    }
+                for (int x = 0; x < DX; ++x) {
+                    vr[kb][i][x] = *reinterpret_cast<const f32x4_t*>(vp + 64 * x);
                 }
             }
-        }
+    };
+    if (L > 0) {
+        load_keys(0);
+        load_k();
+        load_v(jn);
+        for (int64_t v0 = 0; v0 < L; v0 += 16 * KB) {
+            int j[KB];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) j[kb] = jn[kb];
+            if (v0 + 16 * KB < L) load_keys(v0 + 16 * KB);
 
-        // ---- one online softmax per head over the unified set
+            // S^T: lane l holds head l%16 at key slots 16 kb + 4 (l/16) + i
+            f32x4_t st[KB];
 #pragma unroll
-        for (int hh = 0; hh < kGMax; ++hh) {
-            if (hh < G) {
-                const float sv = valid ? s[hh] : -INFINITY;
-                const float mn = fmaxf(m[hh], wave_max(sv));
-                // No valid entry yet (every index so far outside [0, N)): the
-                // reference stays -inf, and a finite stand-in keeps corr and p
-                // at 0 instead of exp2(-inf - -inf) = NaN.
-                const float mc = mn == -INFINITY ? 0.f : mn;
-                const float corr = exp2f(m[hh] - mc);
-                const float p = exp2f(sv - mc);
-                l[hh] = l[hh] * corr + wave_sum(p);
+            for (int kb = 0; kb < KB; ++kb) st[kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < DPL; ++e) acc[hh][e] *= corr;
-                m[hh] = mn;
-                ps[lane][hh] = p;
-            }
-        }
-        __syncthreads();
+            for (int s = 0; s < SL; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb)
+                        st[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[kb][s][e], qf[s][e], st[kb], 0, 0, 0);
+            if (v0 + 16 * KB < L) load_k();
 
-        // ---- PV: lane owns dims [lane*DPL, lane*DPL + DPL)
-        const int64_t doff = (int64_t)lane * DPL;
-        int c = 0;
-        for (; c + 4 <= cnt; c += 4) {
-            float vv[4][DPL];
+            // one online softmax step (scores in the log2 domain)
+            float mx = -INFINITY;
+            uint32_t ok[KB];           // the half's valid slots
+            bool whole = true;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int jc = __builtin_amdgcn_readlane(j, c + u);
-                load_dims<BF16, DPL>(Vbase, (int64_t)jc * D + doff, vv[u]);
-            }
+            for (int kb = 0; kb < KB; ++kb) {
+                ok[kb] = (uint32_t)(__ballot(j[kb] >= 0) & 0xFFFFull);
+                whole = whole && ok[kb] == 0xFFFFu;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float4 p0 = *reinterpret_cast<const float4*>(&ps[c + u][0]);
-                const float4 p1 = *reinterpret_cast<const float4*>(&ps[c + u][4]);
-                const float pp[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-#pragma unroll
-                for (int hh = 0; hh < kGMax; ++hh) {
-                    if (hh < G) {
-#pragma unroll
-                        for (int e = 0; e < DPL; ++e) acc[hh][e] = fmaf(pp[hh], vv[u][e], acc[hh][e]);
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    if (!((ok[kb] >> (4 * lg + i)) & 1u)) st[kb][i] = -INFINITY;
+                    mx = fmaxf(mx, st[kb][i]);
                 }
             }
-        }
-        for (; c < cnt; ++c) {
-            float vv[DPL];
-            const int jc = __builtin_amdgcn_readlane(j, c);
-            load_dims<BF16, DPL>(Vbase, (int64_t)jc * D + doff, vv);
-            const float4 p0 = *reinterpret_cast<const float4*>(&ps[c][0]);
-            const float4 p1 = *reinterpret_cast<const float4*>(&ps[c][4]);
-            const float pp[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+            const float m_new = fmaxf(m_run, quad_max16(mx));
+            // No valid entry yet: a finite stand-in keeps the weights and the
+            // rescale at 0 instead of exp2(-inf - -inf) = NaN.
+            const float mc = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m_run - mc);
+            float ps = 0.f;
 #pragma unroll
-            for (int hh = 0; hh < kGMax; ++hh) {
-                if (hh < G) {
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                    for (int e = 0; e < DPL; ++e) acc[hh][e] = fmaf(pp[hh], vv[e], acc[hh][e]);
+                for (int i = 0; i < 4; ++i) {
+                    st[kb][i] = __builtin_amdgcn_exp2f(st[kb][i] - mc);
+                    ps += st[kb][i];
+                }
+            l_run = l_run * alpha + ps;
+            if (__ballot(m_new != m_run) != 0ull) {           // some head's max moved (or is NaN)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float al = __shfl(alpha, 4 * lg + i);   // of head 4 (l/16) + i
+#pragma unroll
+                    for (int x = 0; x < 4 * DX; ++x) o[x][i] *= al;
                 }
             }
+            m_run = m_new;
+            // Slots without a key carry weight 0; their rows must not bring in
+            // another row's infinities.
+            if (!whole) {
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (!((ok[kb] >> (4 * lg + i)) & 1u)) {
+#pragma unroll
+                            for (int x = 0; x < DX; ++x) vr[kb][i][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+            }
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int x = 0; x < DX; ++x)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            o[4 * x + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[kb][i], vr[kb][i][x][e], o[4 * x + e],
+                                                                              0, 0, 0);
+            if (v0 + 16 * KB < L) load_v(jn);
         }
-        __syncthreads();
     }
 
     // ---- normalise and store
+    l_run = quad_sum16(l_run);
 #pragma unroll
-    for (int hh = 0; hh < kGMax; ++hh) {
-        if (hh < G) {
-            const float inv = l[hh] > 0.f ? 1.0f / l[hh] : 0.f;
-            const int64_t o = ((int64_t)(g * G + hh) * N + q) * D + (int64_t)lane * DPL;
+    for (int i = 0; i < 4; ++i) {
+        const int h = 4 * lg + i;
+        const float lh = __shfl(l_run, h);
+        if (h < G) {
+            const float inv = lh > 0.f ? 1.0f / lh : 0.f;
+            const int64_t base = ((int64_t)(g * G + h) * N + q) * D + 4 * li;
 #pragma unroll
-            for (int e = 0; e < DPL; ++e) {
-                const float val = acc[hh][e] * inv;
-                if (a.out_bf16) static_cast<uint16_t*>(a.out)[o + e] = f32_to_bf16(val);
-                else static_cast<float*>(a.out)[o + e] = val;
+            for (int x = 0; x < DX; ++x) {
+                const f32x4_t y = f32x4_t{o[4 * x][i], o[4 * x + 1][i], o[4 * x + 2][i], o[4 * x + 3][i]} * inv;
+                if (a.out_bf16)
+                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + base + 64 * x) =
+                        make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+                else
+                    *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.out) + base + 64 * x) = y;
             }
         }
     }
@@ -423,7 +411,7 @@ hipError_t launch_attn_gather(const AttnParams& a, hipStream_t st) {
         else hipLaunchKernelGGL((k_attn_gather16<64>), grid, block, 0, st, a, qscale);
         return hipGetLastError();
     }
-    const dim3 grid((unsigned)((int64_t)a.Hkv * a.N)), block(64);
+    const dim3 grid((unsigned)(((int64_t)a.Hkv * a.N + kFWaves - 1) / kFWaves)), block(64 * kFWaves);
     if (a.D == 128) hipLaunchKernelGGL((k_attn_gather<128>), grid, block, 0, st, a, qscale);
     else hipLaunchKernelGGL((k_attn_gather<64>), grid, block, 0, st, a, qscale);
     return hipGetLastError();

@@ -329,3 +329,29 @@ def test_gather_ignores_indices_outside_the_sequence(dtype):
     err = float(np.abs(got - want).max())
     say(f"  out-of-range entries ({dtype}): max err {err:.3e}")
     assert err <= (1e-5 if dtype == "f32" else tight_tol(1, float(np.abs(Vt.float().numpy()).max())))
+
+
+@pytest.mark.parametrize("G", [1, 5, 8])
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_gather_tile_edges(D, G):
+    """Row lengths 0..70 (ends of 16- and 32-key tiles, and of tiles after
+    them) in float32, with a key that no row holds carrying infinities: slots
+    past a row's end must not bring it in.  Bar: 1e-5, the float32 bar."""
+    from oracle import attention as o_att
+    ris = need_gpu()
+    Hkv, N = 2, 71
+    Hq = G * Hkv
+    say(f"f32 gather edges D={D} G={G}")
+    rng = np.random.default_rng(D + G)
+    rows = [np.sort(1 + rng.choice(N - 1, size=r % N, replace=False)).astype(np.int32) for r in range(Hkv * N)]
+    rp = np.zeros(Hkv * N + 1, dtype=np.int64)
+    rp[1:] = np.cumsum([len(x) for x in rows])
+    ci = np.concatenate(rows)
+    Q, K, V = gaussian_qkv(Hq, Hkv, N, D, seed=6)
+    want = o_att.sparse_attention(Q, K, V, rp, ci)
+    K[:, 0], V[:, 0] = np.inf, -np.inf
+    qd, kd, vd = (torch.from_numpy(x).cuda() for x in (Q, K, V))
+    out = torch.full((Hq, N, D), 7.0, dtype=torch.float32, device="cuda")
+    ris.sparse_attn(qd, kd, vd, torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), out,
+                    ris.attn_desc(qd, kd, out, causal=0))
+    assert float(np.abs(out.cpu().numpy() - want).max()) <= 1e-5
