@@ -63,7 +63,7 @@ struct KVTile {
     uint32_t valid;       // bit 16 kb + i: key slot 16 kb + i is a real key
 };
 
-template <int D>
+template <int D, bool STREAM>
 __device__ __forceinline__ void load_tile(const RowSegs& r, const uint16_t* Kr, const uint16_t* Vr,
                                           int64_t v0, int li, int lg, KVTile<D>& T) {
     uint32_t vm = 0;
@@ -80,13 +80,14 @@ __device__ __forceinline__ void load_tile(const RowSegs& r, const uint16_t* Kr, 
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) {
             const int jv = __shfl((int)jj, KPI * s + lane / LPR);
-            T.v[kb][s] = *reinterpret_cast<const u32x4_t*>(Vr + (int64_t)jv * D + 8 * (lane % LPR));
+            const u32x4_t* vp = reinterpret_cast<const u32x4_t*>(Vr + (int64_t)jv * D + 8 * (lane % LPR));
+            T.v[kb][s] = STREAM ? __builtin_nontemporal_load(vp) : *vp;
         }
     }
     T.valid = vm;
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeParams p, float c) {
     constexpr int SL = D / 32;         // k-slices of the score product
     constexpr int DB = D / 16;         // 16-dim blocks of the output
@@ -144,11 +145,11 @@ __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeP
     const int64_t v_first = part * kTileKeys;
     if (v_first < total) {
         KVTile<D> cur;
-        load_tile<D>(r, Kr, Vr, v_first, li, lg, cur);
+        load_tile<D, STREAM>(r, Kr, Vr, v_first, li, lg, cur);
         for (int64_t v0 = v_first; v0 < total; v0 += stride) {
             KVTile<D> nxt;
             const bool more = v0 + stride < total;
-            if (more) load_tile<D>(r, Kr, Vr, v0 + stride, li, lg, nxt);
+            if (more) load_tile<D, STREAM>(r, Kr, Vr, v0 + stride, li, lg, nxt);
 
             // V rows into this wave's LDS, row-major.
 #pragma unroll
@@ -319,11 +320,21 @@ __global__ __launch_bounds__(kCombineThreads) void k_decode_combine(DecodeParams
     }
 }
 
+// K and V bytes of a step from which V is read past the caches (non-temporal
+// loads of whole rows; K's 64-byte pieces need the cache for a row's other
+// pieces).  A step of more than the last-level cache holds (256 MB) finds nothing
+// of it there: 32 sequences at 64k, 1.1 GB, 188 against 170 us; one sequence, 35
+// MB that a following step may still find, 16.7 against 17.0 us.
+constexpr int64_t kStreamBytes = 256ll << 20;
+
 template <int D>
 hipError_t launch_d(const DecodeParams& p, float c, hipStream_t st) {
     const dim3 grid((unsigned)(p.parts / kDecodeWaves), (unsigned)(p.B * p.Hkv));
     if (p.parts % kDecodeWaves != 0 || p.parts > kDecodeMaxParts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_decode_partial<D>, grid, dim3(64 * kDecodeWaves), 0, st, p, c);
+    if (p.kv_bytes > kStreamBytes)
+        hipLaunchKernelGGL((k_decode_partial<D, true>), grid, dim3(64 * kDecodeWaves), 0, st, p, c);
+    else
+        hipLaunchKernelGGL((k_decode_partial<D, false>), grid, dim3(64 * kDecodeWaves), 0, st, p, c);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_decode_combine<D>, dim3((unsigned)((int64_t)p.B * p.Hq)), dim3(kCombineThreads), 0, st, p,

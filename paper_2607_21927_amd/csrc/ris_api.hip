@@ -298,15 +298,20 @@ int ris_sparse_attn(const void* Q, const void* K, const void* V, const int64_t* 
 
 namespace {
 
+// Keys of a typical row: the anchor slice shared evenly by the kv heads, plus
+// window and initial tokens.
+int64_t decode_keys(const ris_decode_desc& d) {
+    const int64_t win = d.window < d.max_len ? d.window : d.max_len;
+    const int64_t snk = d.sink < d.max_len ? d.sink : d.max_len;
+    return (d.anchor_stride + d.Hkv - 1) / d.Hkv + win + snk;
+}
+
 // Waves per row (the workspace has room for a partial of each; a workgroup's
 // waves write one together).  Any value covers every key (the tiles are dealt
 // round-robin); this one aims at ~2048 resident waves over the batch without
-// giving a wave less than one tile of a typical row (the anchor slice shared
-// evenly by the kv heads, plus window and initial tokens).
+// giving a wave less than one tile of a typical row.
 int64_t decode_parts(const ris_decode_desc& d) {
-    const int64_t win = d.window < d.max_len ? d.window : d.max_len;
-    const int64_t snk = d.sink < d.max_len ? d.sink : d.max_len;
-    const int64_t keys = (d.anchor_stride + d.Hkv - 1) / d.Hkv + win + snk;
+    const int64_t keys = decode_keys(d);
     const int64_t tiles = (keys + ris::kDecodeTileKeys - 1) / ris::kDecodeTileKeys;
     const int64_t rows = (int64_t)d.batch * d.Hkv;
     int64_t parts = (ris::kDecodeTargetWaves + rows - 1) / rows;
@@ -430,6 +435,9 @@ int ris_decode_attn(const void* Q, const void* K, const void* V, const int64_t* 
     p.out_bf16 = d.dtype_out == RIS_BF16;
     p.window = d.window; p.sink = d.sink;
     p.parts = (int32_t)decode_parts(d);
+    // a row holds max_len keys at most: no overflow for any descriptor
+    const int64_t keys = decode_keys(d) < d.max_len ? decode_keys(d) : d.max_len;
+    p.kv_bytes = (int64_t)d.batch * d.Hkv * keys * d.D * 4;
     p.scale = d.scale > 0.0f ? d.scale : 1.0f / sqrtf((float)d.D);
     const int64_t n_o = (int64_t)d.batch * d.Hkv * p.parts * p.G * d.D;
     p.part_o = static_cast<float*>(workspace);

@@ -110,6 +110,7 @@ struct DecodeParams {
     int32_t B, Hq, Hkv, G, D;
     int32_t out_bf16;
     int32_t window, sink;
+    int64_t kv_bytes;             // K and V bytes of a step, estimated as for `parts`
     int32_t parts;                // waves per row (a multiple of kDecodeWaves)
     float scale;
 };

@@ -232,3 +232,28 @@ def test_decode_large_batch_many_tiles_per_wave():
     err = float(np.abs(got - want).max())
     say(f"  batch-64 decode max err {err:.3e}")
     assert err <= tight_tol(vmax)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_decode_streamed_caches(D):
+    """More K and V than the last-level cache holds: V is read past the caches.
+    Window only, ragged positions, against float64 on the device."""
+    ris = need_gpu()
+    B, Hq, Hkv, max_len = 40, 4, 2, 6600 * 128 // D + 7
+    say(f"decode streamed D={D}")
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    Q = torch.randn(B, Hq, D, generator=gen, device="cuda").bfloat16()
+    K, V = (torch.empty(B, Hkv, max_len, D, dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in "KV")
+    assert 4 * K.numel() > 256 << 20
+    ts = [max_len - 1 - 37 * b for b in range(B)]
+    pos = torch.tensor(ts, dtype=torch.int64, device="cuda")
+    out = torch.empty(B, Hq, D, dtype=torch.float32, device="cuda")
+    dd = ris.decode_desc(Q, K, out, 0, window=max_len)
+    ws = torch.empty(ris.decode_workspace_bytes(dd), dtype=torch.uint8, device="cuda")
+    ris.decode_attn(Q, K, V, pos, torch.zeros(B * (Hkv + 1), dtype=torch.int64, device="cuda"),
+                    torch.zeros(1, dtype=torch.int32, device="cuda"), out, ws, dd)
+    for b in range(0, B, 3):
+        for g in range(Hkv):
+            k, v = K[b, g, :ts[b] + 1].double(), V[b, g, :ts[b] + 1].double()
+            p = torch.softmax(Q[b, 2 * g:2 * g + 2].double() @ k.t() / D**0.5, -1)
+            assert float((out[b, 2 * g:2 * g + 2] - p @ v).abs().max()) <= tight_tol(float(v.abs().max()))

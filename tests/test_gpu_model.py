@@ -145,3 +145,21 @@ def test_host_layers_at_vector_edges(dtype, rows, cols, off):
     g = gu.double()
     want = torch.nn.functional.silu(g[:, :cols]) * g[:, cols:]
     assert (m.double() - want).abs().le(u * want.abs() + 1e-30).all()
+
+
+def test_swiglu_streamed():
+    """Tensors of more than twice the last-level cache, read and written past
+    the caches; a last workgroup of a few vectors.  Bar as above."""
+    ris = need_gpu()
+    rows, inter = 10001, 9000
+    say("swiglu streamed")
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    gu = torch.empty(rows, 2 * inter, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    m = torch.empty(rows, inter, dtype=torch.bfloat16, device="cuda")
+    assert 2 * (gu.numel() + m.numel()) > 512 << 20
+    ris.swiglu(gu, m)
+    u = 2.0**-8 + 32 * 2.0**-24
+    for r in range(0, rows, 1000):
+        g = gu[r:r + 1000].double()
+        want = torch.nn.functional.silu(g[:, :inter]) * g[:, inter:]
+        assert (m[r:r + 1000].double() - want).abs().le(u * want.abs() + 1e-30).all()
