@@ -1,7 +1,8 @@
 // Status words of the one-pass geometry build's decoupled look-back.
 //
-// Row r of the build publishes its status in row_ptr[r + 1] while the build
-// runs; the flags are stripped afterwards.  A status is
+// A row of the build publishes its status in row_ptr[r + 1] while the build
+// runs (where workgroups build chunks of rows: a chunk, in its last row's
+// entry); the flags are stripped afterwards.  A status is
 //   0                     nothing known yet,
 //   kAgg | count          the row's own size is known,
 //   kInc | prefix         the inclusive prefix (offset of the next row) is known,
