@@ -80,79 +80,132 @@ __global__ __launch_bounds__(kNormThreads) void k_rmsnorm(const void* x, void* r
     }
 }
 
-// The same on rows of whole, aligned 16-byte vectors (kVec elements).  kWaves
-// waves own a row and hold it in registers (kRegs vectors a lane), so x and
-// residual are read once and nothing is read back: HBM-bound.  A wave to a row
-// needs no barrier; 256 / kWaves / 64 rows share a workgroup.  32,768 rows of
-// 1,536 bf16 with the residual: 254 us with one element per access, 70 us as
-// vectors (5.7 TB/s).
-template <bool BF16, int kWaves, int kRegs>
-__global__ __launch_bounds__(kNormThreads) void k_rmsnorm_vec(const void* x, void* residual, const void* w, void* out,
-                                                              int64_t rows, int cols, float eps) {
+// The same on rows of whole, aligned 16-byte vectors, to the same bits: thread t
+// of the form above adds the squares of the columns t, t + 256, .. in turn, and
+// the two forms below keep these chains and the order in which they meet.  A row
+// stays in registers as stored (kRegs vectors a lane), so x and residual are
+// read once and nothing is read back, and the weights come in beside the row:
+// HBM-bound.  32,768 rows of 1,536 bf16 with the residual: 254 us with one
+// element per access, 70 us as vectors (5.7 TB/s).
+
+// r[i] <- vector first + i * kStep of x (+ residual, stored back), g[i] <- of w.
+template <bool BF16, int kRegs, int kStep>
+__device__ __forceinline__ void load_row(const void* x, void* residual, const void* w, int64_t base, int first, int nv,
+                                         u32x4_t (&r)[kRegs], u32x4_t (&g)[kRegs]) {
     constexpr int kVec = kVecElts<BF16>;
-    constexpr int kRowThreads = 64 * kWaves;
-    __shared__ float red[kNormThreads / 64];
-    const int t = threadIdx.x % kRowThreads;
-    const int64_t row = (int64_t)blockIdx.x * (kNormThreads / kRowThreads) + threadIdx.x / kRowThreads;
-    if (row >= rows) return;                          // whole waves, and whole workgroups where waves share a row
+    u32x4_t* res = static_cast<u32x4_t*>(residual);
+    u32x4_t old[kRegs];
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) {
+        const int v = first + i * kStep;
+        if (v < nv) {
+            r[i] = static_cast<const u32x4_t*>(x)[base + v];
+            if (residual) old[i] = res[base + v];
+            g[i] = static_cast<const u32x4_t*>(w)[v];
+        }
+    }
+    if (!residual) return;
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) {
+        const int v = first + i * kStep;
+        if (v < nv) {
+            float f[kVec], o[kVec];
+            unpack_vec<BF16>(r[i], f);
+            unpack_vec<BF16>(old[i], o);
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) f[e] += o[e];
+            r[i] = pack_vec<BF16>(f);                 // the norm sees the stored values
+            res[base + v] = r[i];
+        }
+    }
+}
+
+template <bool BF16, int kRegs, int kStep>
+__device__ __forceinline__ void store_row(void* out, int64_t base, int first, int nv, float inv,
+                                          const u32x4_t (&r)[kRegs], const u32x4_t (&g)[kRegs]) {
+    constexpr int kVec = kVecElts<BF16>;
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i) {
+        const int v = first + i * kStep;
+        if (v < nv) {
+            float f[kVec], y[kVec];
+            unpack_vec<BF16>(r[i], f);
+            unpack_vec<BF16>(g[i], y);
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) y[e] = f[e] * inv * y[e];
+            static_cast<u32x4_t*>(out)[base + v] = pack_vec<BF16>(y);
+        }
+    }
+}
+
+// 256 / kVec lanes own a row: element e of a lane's vectors (the columns kVec *
+// lane + e, then 256 further on, ..) is one chain, kept in the lane.  No barrier.
+template <bool BF16, int kRegs>
+__global__ __launch_bounds__(kNormThreads, 4)
+void k_rmsnorm_lanes(const void* x, void* residual, const void* w, void* out, int64_t rows, int cols, float eps) {
+    constexpr int kVec = kVecElts<BF16>;
+    constexpr int kLanes = kNormThreads / kVec;       // a row's lanes: 32 bf16, 64 float32
+    const int t = threadIdx.x % kLanes;
+    const int64_t row = (int64_t)blockIdx.x * (kNormThreads / kLanes) + threadIdx.x / kLanes;
+    if (row >= rows) return;                          // all of a row's lanes
     const int nv = cols / kVec;
     const int64_t base = row * nv;
-    float r[kRegs][kVec];
-    float ss = 0.f;
+    u32x4_t r[kRegs], g[kRegs];
+    load_row<BF16, kRegs, kLanes>(x, residual, w, base, t, nv, r, g);
+    float ss[kVec];
 #pragma unroll
-    for (int i = 0; i < kRegs; ++i) {
-        const int v = t + i * kRowThreads;
-        if (v < nv) unpack_vec<BF16>(static_cast<const u32x4_t*>(x)[base + v], r[i]);
-    }
-    if (residual) {
-        u32x4_t* res = static_cast<u32x4_t*>(residual);
-        u32x4_t old[kRegs];
-#pragma unroll
-        for (int i = 0; i < kRegs; ++i) {
-            const int v = t + i * kRowThreads;
-            if (v < nv) old[i] = res[base + v];
-        }
-#pragma unroll
-        for (int i = 0; i < kRegs; ++i) {
-            const int v = t + i * kRowThreads;
-            if (v < nv) {
-                float o[kVec];
-                unpack_vec<BF16>(old[i], o);
-#pragma unroll
-                for (int e = 0; e < kVec; ++e) r[i][e] += o[e];
-                const u32x4_t sum = pack_vec<BF16>(r[i]);
-                res[base + v] = sum;
-                unpack_vec<BF16>(sum, r[i]);          // the norm sees the stored values
-            }
-        }
-    }
+    for (int e = 0; e < kVec; ++e) ss[e] = 0.f;
 #pragma unroll
     for (int i = 0; i < kRegs; ++i)
-        if (t + i * kRowThreads < nv) {
+        if (t + i * kLanes < nv) {
+            float f[kVec];
+            unpack_vec<BF16>(r[i], f);
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) ss += r[i][e] * r[i][e];
+            for (int e = 0; e < kVec; ++e) ss[e] = fmaf(f[e], f[e], ss[e]);
         }
-    float tot = wave_sum(ss);
-    if constexpr (kWaves > 1) {
-        static_assert(kWaves == 1 || kWaves * 64 == kNormThreads, "one row per workgroup where waves share it");
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = tot;
-        __syncthreads();
-        tot = 0.f;
+    // the butterfly of 64 neighbouring chains (wave_sum there), then the four in turn
+    float s = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    if constexpr (BF16) s += (ss[4] + ss[5]) + (ss[6] + ss[7]);
+    s += dpp<0xB1>(s, 0.0f);                          // quad_perm [1,0,3,2]
+    s += dpp<0x4E>(s, 0.0f);                          // quad_perm [2,3,0,1]
+    s += dpp<0x141>(s, 0.0f);                         // row_half_mirror
+    if constexpr (!BF16) s += dpp<0x140>(s, 0.0f);    // row_mirror
+    float tot = 0.f;
 #pragma unroll
-        for (int i = 0; i < kNormThreads / 64; ++i) tot += red[i];
+    for (int i = 0; i < kNormThreads / 64; ++i) tot += __shfl(s, i * (64 / kVec), kLanes);
+    store_row<BF16, kRegs, kLanes>(out, base, t, nv, rsqrtf(tot / (float)cols + eps), r, g);
+}
+
+// A workgroup to a row.  The vectors pass through LDS once, where each thread
+// reads its chain's columns.
+template <bool BF16, int kRegs>
+__global__ __launch_bounds__(kNormThreads, 4)
+void k_rmsnorm_wide(const void* x, void* residual, const void* w, void* out, int cols, float eps) {
+    constexpr int kVec = kVecElts<BF16>;
+    __shared__ u32x4_t vals[kRegs * kNormThreads];
+    __shared__ float red[kNormThreads / 64];
+    const int t = threadIdx.x, nv = cols / kVec;
+    const int64_t base = (int64_t)blockIdx.x * nv;
+    u32x4_t r[kRegs], g[kRegs];
+    load_row<BF16, kRegs, kNormThreads>(x, residual, w, base, t, nv, r, g);
+#pragma unroll
+    for (int i = 0; i < kRegs; ++i)
+        if (t + i * kNormThreads < nv) vals[t + i * kNormThreads] = r[i];
+    __syncthreads();
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < kRegs * kVec; ++k) {
+        const int c = t + k * kNormThreads;
+        const float f = load_elt(vals, c, BF16);      // past the row: inside vals, and not used
+        ss = c < cols ? fmaf(f, f, ss) : ss;
     }
-    const float inv = rsqrtf(tot / (float)cols + eps);
+    ss = wave_sum(ss);
+    if ((t & 63) == 0) red[t >> 6] = ss;
+    __syncthreads();
+    float tot = 0.f;
 #pragma unroll
-    for (int i = 0; i < kRegs; ++i) {
-        const int v = t + i * kRowThreads;
-        if (v < nv) {
-            float g[kVec];
-            unpack_vec<BF16>(static_cast<const u32x4_t*>(w)[v], g);
-#pragma unroll
-            for (int e = 0; e < kVec; ++e) g[e] = r[i][e] * inv * g[e];
-            static_cast<u32x4_t*>(out)[base + v] = pack_vec<BF16>(g);
-        }
-    }
+    for (int i = 0; i < kNormThreads / 64; ++i) tot += red[i];
+    store_row<BF16, kRegs, kNormThreads>(out, base, t, nv, rsqrtf(tot / (float)cols + eps), r, g);
 }
 
 // Element by element, where rows are no whole, aligned vectors:
@@ -203,35 +256,37 @@ __global__ __launch_bounds__(256) void k_swiglu_vec(const u32x4_t* gu, u32x4_t* 
     }
 }
 
-template <bool BF16, int kWaves>
-void run_rmsnorm_vec(int regs, const void* x, void* residual, const void* w, void* out, int64_t rows, int cols,
-                     float eps, hipStream_t st) {
-    const int64_t per = kNormThreads / (64 * kWaves);
-    const dim3 grid((unsigned)((rows + per - 1) / per)), block(kNormThreads);
-    switch (regs) {
-        case 1: hipLaunchKernelGGL((k_rmsnorm_vec<BF16, kWaves, 1>), grid, block, 0, st, x, residual, w, out, rows, cols, eps); break;
-        case 2: hipLaunchKernelGGL((k_rmsnorm_vec<BF16, kWaves, 2>), grid, block, 0, st, x, residual, w, out, rows, cols, eps); break;
-        case 3: hipLaunchKernelGGL((k_rmsnorm_vec<BF16, kWaves, 3>), grid, block, 0, st, x, residual, w, out, rows, cols, eps); break;
-        default: hipLaunchKernelGGL((k_rmsnorm_vec<BF16, kWaves, 4>), grid, block, 0, st, x, residual, w, out, rows, cols, eps); break;
-    }
-}
-
-// Rows of whole vectors that four waves' registers can hold (kMaxRegs vectors
-// a lane: 8,192 bf16 or 4,096 float32 columns).
-constexpr int kMaxRegs = 4;
+// Rows of whole vectors, up to 8,192 bf16 or 4,096 float32 columns.  A workgroup to
+// a row has more loads in flight where rows are few (256 rows of 1,536 bf16 with
+// the residual: 2.9 against 4.6 us), 32 lanes to a row cost less where they are
+// many (16,384 rows of 1,000: 20.8 against 22.6); 64 lanes gain nothing on float32
+// rows of more than two vectors a lane (16,384 of 1,536: 60.6 against 63.3).
 template <bool BF16>
 bool rmsnorm_vec(const void* x, void* residual, const void* w, void* out, int64_t rows, int64_t cols, float eps,
                  hipStream_t st) {
-    constexpr int kVec = kVecElts<BF16>;
+    constexpr int kVec = kVecElts<BF16>, kLanes = kNormThreads / kVec, kPer = kNormThreads / kLanes;
+    constexpr int64_t kManyRows = 4096;
     if (cols % kVec != 0 || !aligned16(x) || !aligned16(residual) || !aligned16(w) || !aligned16(out)) return false;
-    const int64_t nv = cols / kVec;
-    if (nv <= 64 * kMaxRegs)
-        run_rmsnorm_vec<BF16, 1>((int)((nv + 63) / 64), x, residual, w, out, rows, (int)cols, eps, st);
-    else if (nv <= kNormThreads * kMaxRegs)
-        run_rmsnorm_vec<BF16, 4>((int)((nv + kNormThreads - 1) / kNormThreads), x, residual, w, out, rows, (int)cols,
-                                 eps, st);
-    else
-        return false;
+    const int64_t nv = cols / kVec, regs = (nv + kLanes - 1) / kLanes, wide = (nv + kNormThreads - 1) / kNormThreads;
+    const dim3 block(kNormThreads);
+    const auto lanes = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + kPer - 1) / kPer)), block, 0, st, x, residual, w, out, rows,
+                           (int)cols, eps);
+    };
+    const auto group = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)rows), block, 0, st, x, residual, w, out, (int)cols, eps);
+    };
+    if (regs <= 2) lanes(k_rmsnorm_lanes<BF16, 2>);
+    else if (BF16 && rows > kManyRows && regs <= 8) {
+        if (regs <= 4) lanes(k_rmsnorm_lanes<true, 4>);
+        else if (regs <= 6) lanes(k_rmsnorm_lanes<true, 6>);
+        else lanes(k_rmsnorm_lanes<true, 8>);
+    }
+    else if (wide <= 1) group(k_rmsnorm_wide<BF16, 1>);
+    else if (wide <= 2) group(k_rmsnorm_wide<BF16, 2>);
+    else if (wide <= 3) group(k_rmsnorm_wide<BF16, 3>);
+    else if (wide <= 4) group(k_rmsnorm_wide<BF16, 4>);
+    else return false;
     return true;
 }
 

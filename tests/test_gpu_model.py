@@ -163,3 +163,37 @@ def test_swiglu_streamed():
         g = gu[r:r + 1000].double()
         want = torch.nn.functional.silu(g[:, :inter]) * g[:, inter:]
         assert (m[r:r + 1000].double() - want).abs().le(u * want.abs() + 1e-30).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(9, 8), (3, 256), (5, 1000), (33, 1536), (8, 2048), (7, 2056), (2, 4096), (3, 8192),
+                                       (4097, 520), (4100, 1096), (4101, 1544), (4099, 2048)])
+def test_host_layers_do_not_depend_on_alignment(dtype, rows, cols):
+    """The forms that read 16-byte vectors, whole or off a 16-byte boundary,
+    give the bits of the element-by-element form (buffers one element further
+    on): the same sums in the same order, the same roundings, subnormal values
+    and sums among them."""
+    ris = need_gpu()
+    say(f"alignment {dtype} rows {rows} cols {cols}")
+    gen = torch.Generator().manual_seed(rows * 10007 + cols)
+
+    def both(n, scale=1.0, shift=0.0):
+        v = (torch.randn(n, generator=gen) * scale + shift).to(dtype).cuda()
+        return v, torch.empty(n + 1, dtype=dtype, device="cuda")[1:].copy_(v)
+
+    def same(pair):
+        a, b = (t.view(torch.int16 if dtype == torch.bfloat16 else torch.int32) for t in pair)
+        return torch.equal(a, b)
+
+    x, r, w, gu = both(rows * cols), both(rows * cols), both(cols, 0.1, 1.0), both(rows * 2 * cols, 4.0)
+    for t in x + r:
+        t[:cols] *= 1e-39
+    out, m = both(rows * cols), both(rows * cols)
+    for i in (0, 1):
+        ris.rmsnorm(x[i].view(rows, cols), w[i], out[i].view(rows, cols), 1e-6)
+        ris.swiglu(gu[i].view(rows, 2 * cols), m[i].view(rows, cols))
+    assert same(out), "rmsnorm"
+    assert same(m), "swiglu"
+    for i in (0, 1):
+        ris.rmsnorm(x[i].view(rows, cols), w[i], out[i].view(rows, cols), 1e-6, residual=r[i].view(rows, cols))
+    assert same(r) and same(out), "rmsnorm with a residual"
