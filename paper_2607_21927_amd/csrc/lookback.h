@@ -65,5 +65,30 @@ RIS_HD inline int step_end(uint64_t inc, uint64_t ready) {
 // The flags stripped: the row's end offset, or -1 for a poisoned row.
 RIS_HD inline int64_t stripped(int64_t s) { return is_poisoned(s) ? -1 : value(s); }
 
+// Entry of row_ptr that holds unit u's status, in a build of R rows by units of
+// `stride` rows each (the last one may hold fewer): that of the unit's last row.
+RIS_HD inline int64_t unit_entry(int64_t u, int64_t stride, int64_t R) {
+    return (u + 1) * stride < R ? (u + 1) * stride : R;
+}
+
+// Strip by one workgroup: `thread` of `threads` strips its share of the units
+// but the last, and says whether one was poisoned.  The last unit's entry is the
+// total, R: once every thread's share is known, one thread stores it, once
+// (total_entry).  Two threads' stores to one entry would land in either order --
+// a workgroup barrier does not wait for stores -- and an incomplete build could
+// be left with a total that looks complete.
+template <class Load, class Store>
+RIS_HD inline bool strip_units(int64_t thread, int64_t threads, int64_t units, int64_t stride, int64_t R, Load load,
+                               Store store) {
+    bool poison = false;
+    for (int64_t u = thread; u < units - 1; u += threads) {
+        const int64_t at = unit_entry(u, stride, R), s = load(at);
+        poison |= is_poisoned(s);
+        store(at, stripped(s));
+    }
+    return poison;
+}
+RIS_HD inline int64_t total_entry(int64_t last_status, bool poison) { return poison ? -1 : stripped(last_status); }
+
 }  // namespace lookback
 }  // namespace ris

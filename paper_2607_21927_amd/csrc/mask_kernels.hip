@@ -700,12 +700,6 @@ __device__ void resolve_and_emit(const MaskParams& p, int64_t* row_ptr, int32_t*
 // With `fold` the last workgroup to finish strips the statuses (the count of
 // finished workgroups lives in the high half of row_ptr[0], the tickets in the
 // low one); otherwise the last ticket restores row_ptr[0].
-__device__ void strip_entry(int64_t* row_ptr, int64_t at, bool& poison) {
-    const int64_t v = status_load(&row_ptr[at]);
-    poison |= lookback::is_poisoned(v);
-    status_store(&row_ptr[at], lookback::stripped(v));
-}
-
 template <int T, int kRows>
 __global__ __launch_bounds__(T * kRows, 8) void k_mask_chunk(MaskParams p, int64_t* row_ptr, int32_t* col_idx,
                                                          int64_t capacity, int fold) {
@@ -793,12 +787,11 @@ __global__ __launch_bounds__(T * kRows, 8) void k_mask_chunk(MaskParams p, int64
     }
     __syncthreads();
     if (!s_last) return;                                      // the same in every thread
-    bool poison = false;
-    for (int64_t c = threadIdx.x; c < (int64_t)gridDim.x; c += T * kRows)
-        strip_entry(row_ptr, (c + 1) * kRows < R ? (c + 1) * kRows : R, poison);
-    const int any = __syncthreads_or(poison);
+    const int any = __syncthreads_or(lb::strip_units(
+        threadIdx.x, T * kRows, gridDim.x, kRows, R, [&](int64_t at) { return status_load(&row_ptr[at]); },
+        [&](int64_t at, int64_t v) { status_store(&row_ptr[at], v); }));
     if (threadIdx.x == 0) {
-        if (any) status_store(&row_ptr[R], -1);
+        status_store(&row_ptr[R], lb::total_entry(status_load(&row_ptr[R]), any));
         status_store(row_ptr, 0);
     }
 }

@@ -9,10 +9,17 @@
 //     its exact offset; a row whose look-back reaches a poisoned prefix is
 //     poisoned; and the stripped total row_ptr[R] is negative exactly when
 //     some row is poisoned.
+//   * the same where one row gives up and rows after it pass it.
+// Where workgroups build chunks of rows, the "rows" of the look-back are chunks
+// whose statuses lie `stride` entries apart, and with few chunks the last
+// workgroup strips the statuses itself: its threads' stores are played in a
+// random order, since nothing but the one thread's own order holds them.
 // Prints one line per case and exits 0 when every check holds.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <random>
+#include <utility>
 #include <vector>
 
 #include "lookback.h"
@@ -35,9 +42,15 @@ struct Result {
     int64_t poisoned = 0;
 };
 
-static Result simulate(int64_t R, uint32_t spin_limit, unsigned seed) {
+// R units of `stride` rows each, the last one of 1 to `stride`.  Unit `gives_up`
+// gives up its look-back whatever it finds; units after it may have passed it by
+// its size alone, and are not poisoned.
+static Result simulate(int64_t R, uint32_t spin_limit, unsigned seed, int64_t stride = 1, bool fold = false,
+                       int64_t gives_up = -1) {
     std::mt19937_64 rng(seed);
-    std::vector<int64_t> status(R + 1, 0);   // status of row r in status[r + 1]
+    const int64_t total_rows = (R - 1) * stride + 1 + (int64_t)(rng() % (uint64_t)stride);
+    std::vector<int64_t> entries(total_rows + 1, 0);         // row_ptr
+    const auto at = [&](int64_t u) { return lb::unit_entry(u, stride, total_rows); };
     std::vector<Row> rows(R);
     std::vector<int64_t> truth(R + 1, 0);
     for (int64_t r = 0; r < R; ++r) {
@@ -59,20 +72,22 @@ static Result simulate(int64_t R, uint32_t spin_limit, unsigned seed) {
         Row& w = rows[r];
         if (w.state == 1) {
             if (w.build_left-- > 0) continue;
-            status[r + 1] = lb::aggregate(w.count);
+            entries[at(r)] = lb::aggregate(w.count);
             w.state = 2;
             continue;
         }
         // one look-back step: "lane" i reads the status of row j - 1 - i
         bool finished = false;
-        if (w.j == 0) {
+        if (r == gives_up) {
+            w.poisoned = finished = true;
+        } else if (w.j == 0) {
             finished = true;
         } else {
             int64_t v[64];
             uint64_t inc = 0, ready = 0;
             for (int i = 0; i < 64; ++i) {
                 const int64_t idx = w.j - i;
-                v[i] = idx > 0 ? status[idx] : lb::inclusive(0, false);
+                v[i] = idx > 0 ? entries[idx * stride] : lb::inclusive(0, false);
                 if (lb::is_inclusive(v[i])) inc |= 1ull << i;
                 if (lb::is_ready(v[i])) ready |= 1ull << i;
             }
@@ -96,21 +111,34 @@ static Result simulate(int64_t R, uint32_t spin_limit, unsigned seed) {
             }
         }
         if (finished) {
-            status[r + 1] = lb::inclusive(w.prefix + w.count, w.poisoned);
+            entries[at(r)] = lb::inclusive(w.prefix + w.count, w.poisoned);
             w.state = 3;
             ++done;
             active.erase(active.begin() + pick);
         }
     }
-    // strip, as k_strip_status does
     Result res;
-    std::vector<int64_t> row_ptr(R + 1, 0);
     bool any = false;
-    for (int64_t i = 1; i <= R; ++i) {
-        any |= lb::is_poisoned(status[i]);
-        row_ptr[i] = lb::stripped(status[i]);
+    if (fold) {
+        // the last workgroup, as k_mask_chunk does
+        const int64_t threads = 64 << rng() % 4;
+        std::vector<std::pair<int64_t, int64_t>> stores;
+        for (int64_t t = 0; t < threads; ++t)
+            any |= lb::strip_units(t, threads, R, stride, total_rows, [&](int64_t e) { return entries[e]; },
+                                   [&](int64_t e, int64_t v) { stores.emplace_back(e, v); });
+        stores.emplace_back(total_rows, lb::total_entry(entries[total_rows], any));
+        std::shuffle(stores.begin(), stores.end(), rng);
+        for (const auto& s : stores) entries[s.first] = s.second;
+    } else {
+        // k_strip_status: every store is done before the total's -1
+        for (int64_t u = 0; u < R; ++u) {
+            any |= lb::is_poisoned(entries[at(u)]);
+            entries[at(u)] = lb::stripped(entries[at(u)]);
+        }
+        if (any) entries[total_rows] = -1;
     }
-    if (any) row_ptr[R] = -1;
+    std::vector<int64_t> row_ptr(R + 1, 0);                  // the units' entries
+    for (int64_t r = 0; r < R; ++r) row_ptr[r + 1] = entries[at(r)];
     for (int64_t r = 0; r < R; ++r) {
         const Row& w = rows[r];
         if (w.poisoned) {
@@ -144,6 +172,16 @@ int main() {
         }
         poisoned_runs += zero.poisoned > 0;
         ++runs;
+        for (const int64_t stride : {1, 4, 8})
+            for (const bool fold : {false, true}) {
+                if (!simulate(R, 1u << 20, seed + 2000, stride, fold).ok ||
+                    !simulate(R, 0, seed + 3000, stride, fold).ok ||
+                    !simulate(R, 1u << 20, seed + 4000, stride, fold, (int64_t)seed * 31 % R).ok) {
+                    std::printf("FAIL stride %lld fold %d: seed %u R %lld\n", (long long)stride, (int)fold, seed,
+                                (long long)R);
+                    ok = false;
+                }
+            }
     }
     std::printf("large limit: %lld runs clean; limit 0: %lld of %lld runs poisoned\n", (long long)runs,
                 (long long)poisoned_runs, (long long)runs);
