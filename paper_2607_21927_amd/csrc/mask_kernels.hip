@@ -971,6 +971,10 @@ constexpr size_t kChunk8Smem = 80 << 10;
 // against 2.07 ms, 150,000 4.36 against 3.39.
 constexpr size_t kWaveSmem = 80 << 10;
 constexpr size_t kWaveSmemTwoPhase = 64 << 10;
+// A dispatch holds fewer than 2^32 work-items, and a wave to a row takes 64 a row
+// (in chunks of up to 8 rows): builds of more rows go to the persistent grid,
+// whose size does not grow with them.
+constexpr int64_t kWaveRows = (1ll << 26) - 8;
 // Builds of at most this many rows leave CUs idle with 256 lanes to a row; 1,024
 // lanes take a row of 46,000 draws in 29 instead of 47 us (2 rows; 512 rows of
 // the same 63 instead of 75, 1,024 rows 109 against 105), and one of 655 in 13
@@ -1045,7 +1049,7 @@ hipError_t launch_mask_fused(const MaskParams& p, int64_t* row_ptr, int32_t* col
     const int64_t rows = (int64_t)p.heads * p.nq, draws = middle_draws(p);
     if (rows <= kFewRows && draws >= kFewRowsDraws)
         return run_mask_chunk<1024, 1>(p, row_ptr, col_idx, capacity, st);
-    if (draws < kWaveDraws && group_smem_bytes<64>(p, 4) <= kWaveSmem) {
+    if (draws < kWaveDraws && rows <= kWaveRows && group_smem_bytes<64>(p, 4) <= kWaveSmem) {
         if (draws < kChunk8Draws && group_smem_bytes<64>(p, 8) <= kChunk8Smem)
             return run_mask_chunk<64, 8>(p, row_ptr, col_idx, capacity, st);
         return run_mask_chunk<64, 4>(p, row_ptr, col_idx, capacity, st);

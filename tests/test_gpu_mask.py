@@ -285,3 +285,24 @@ def test_mask_rows_at_dispatch_edges(case, fused):
     assert np.array_equal(rp_h, np.concatenate([[0], np.cumsum([len(w) for w in want])]))
     assert np.array_equal(ci_h[:rp_h[-1]], np.concatenate(want))
     assert (ci_h[rp_h[-1]:] == -9).all()
+
+
+def test_mask_more_rows_than_a_dispatch_has_waves():
+    """2^26 rows, more than one dispatch's 2^32 work-items hold at a wave to a
+    row: built all the same.  One draw a row, so row r ends at r + 1."""
+    ris = need_gpu()
+    heads, N = 8192, 8192
+    sp = spec_of(0, 1, N, heads, 1, 5)
+    say(f"mask {heads} heads x {N} rows")
+    d = desc_of(ris, sp)
+    R = heads * N
+    assert ris.mask_nnz_bound(d) == R
+    rp = torch.full((R + 1,), -7, dtype=torch.int64, device="cuda")
+    ci = torch.full((R,), -9, dtype=torch.int32, device="cuda")
+    ris.mask_build(d, rp, ci)
+    assert torch.equal(rp, torch.arange(R + 1, device="cuda"))
+    keys = ci.view(heads, N)
+    assert bool((keys >= 0).all()) and bool((keys <= torch.arange(N, device="cuda", dtype=torch.int32)).all())
+    for h in (0, 4095, 8191):
+        want = np.concatenate(o_geo.row_sets(sp, h, np.arange(N)))
+        assert np.array_equal(keys[h].cpu().numpy(), want)
