@@ -149,13 +149,14 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void k_attn_gather(AttnParams a, f
             // No valid entry yet: a finite stand-in keeps the weights and the
             // rescale at 0 instead of exp2(-inf - -inf) = NaN.
             const float mc = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run - mc);
+            // exp2f, not the bare instruction: a weight below 2^-126 times a large value counts in float32
+            const float alpha = exp2f(m_run - mc);
             float ps = 0.f;
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    st[kb][i] = __builtin_amdgcn_exp2f(st[kb][i] - mc);
+                    st[kb][i] = exp2f(st[kb][i] - mc);
                     ps += st[kb][i];
                 }
             l_run = l_run * alpha + ps;

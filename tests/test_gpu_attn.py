@@ -355,3 +355,28 @@ def test_f32_gather_tile_edges(D, G):
     ris.sparse_attn(qd, kd, vd, torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), out,
                     ris.attn_desc(qd, kd, out, causal=0))
     assert float(np.abs(out.cpu().numpy() - want).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_gather_subnormal_weights(D):
+    """Weights below 2^-126 (a key 90 below the row's maximum, e^-90 = 2^-129.8)
+    and subnormal values count: with values of 1e38 such a key decides the row's
+    output.  The weight holds no fewer than 19 bits of a float32's 24 (spacing
+    2^-149), so the bar is 2^-19 plus exp2's and the exponent's own errors (the
+    exponent 129.8 is a float32, 2^-17 of absolute error, times ln 2): 2e-5."""
+    ris = need_gpu()
+    say(f"f32 gather subnormal weights D={D}")
+    N = 40
+    rp = torch.arange(0, 2 * N + 1, 2, dtype=torch.int64, device="cuda")
+    ci = torch.tensor([0, 1] * N, dtype=torch.int32, device="cuda")
+    q, k, v = (torch.zeros(1, N, D, device="cuda") for _ in "qkv")
+    out = torch.empty(1, N, D, device="cuda")
+    q[:, :, 0], k[0, 0, 0], v[0, 1] = 1.0, 90.0, 1e38
+    ad = ris.attn_desc(q, k, out, causal=0, scale=1.0)
+    ris.sparse_attn(q, k, v, rp, ci, out, ad)
+    want = float(v[0, 1, 0].double() * torch.exp(torch.tensor(-90.0, dtype=torch.float64)))
+    assert float((out.double() / want - 1.0).abs().max()) <= 2e-5
+    k.zero_()
+    v[0, 0] = v[0, 1] = 1e-39
+    ris.sparse_attn(q, k, v, rp, ci, out, ad)
+    assert torch.equal(out, v[:, :1].expand_as(out))
