@@ -21,36 +21,35 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // float32 gather on the matrix unit: one wavefront per (kv_head g, query row
-// q), four rows per workgroup, no LDS.  The row's set is walked in tiles of
-// 16 keys at D = 128 and 32 at D = 64 (32 registers each of K and of V):
+// q), a workgroup of its own, no LDS.  The row's set is walked in tiles of 16
+// keys:
 //   * S^T = K Q^T on MFMA 16x16x4 f32 with the G query heads of the group as
 //     the 16-wide dimension; lane l loads key l%16's dims 16 s + 4 (l/16) ..
 //     as one 16-byte vector and product e of a slice takes element e of it, so
 //     both operands come straight from memory in that order of the dims;
 //   * one online softmax per head (lane l owns head l%16);
-//   * O += P V on the same MFMA: product i of a 16-key half takes the keys
-//     4 (l/16) + i, whose weights lane l holds already, and lane l loads those
-//     rows' dims 64 x + 4 (l%16) .. , whole rows over 16 lanes.
+//   * O += P V on the same MFMA: product i takes the keys 4 (l/16) + i, whose
+//     weights lane l holds already, and lane l loads those rows' dims
+//     64 x + 4 (l%16) .. , whole rows over 16 lanes.
 // The next tile's K rows are loaded once the scores are formed, its V rows once
-// the outputs are.  Bound by the gathers (the matrix unit is busy about 40%, its
-// 16 columns filled by G heads).  12/2 heads, D = 128, N = 4,096, 10 seeds at
-// 1%: 363 us with a lane to a key (K rows read 16 bytes per lane and load,
-// scores and outputs on the vector unit), 205 us here: 8 TB/s of K and V rows.
-// An XCD's workgroups kept to one head's rows (its L2 then holds that head's K
-// and V) measured the same.
+// the outputs are.  Bound by the gathers, and by latency where rows are light.
+// 12/2 heads, D = 128, N = 4,096, 10 seeds at 1%: 337 us with a lane to a key (K
+// rows read 16 bytes per lane and load, scores and outputs on the vector unit),
+// 173 us here: 9.5 TB/s of K and V rows.  With four rows to a workgroup, which
+// ends with its slowest, 198; and with tiles of 32 keys at D = 64 light rows were
+// slower than with a lane to a key: 8/8 heads, D = 64, N = 4,096, one seed at 1%
+// (20 keys a row) 85 us against 64, here 59; ten seeds 340, 362 and 294.  An XCD's
+// workgroups kept to one head's rows (its L2 then holds that head's K and V)
+// measured the same.
 // ---------------------------------------------------------------------------
-constexpr int kFWaves = 4;            // rows (waves) per workgroup
-
 template <int D>
-__global__ __launch_bounds__(64 * kFWaves, 3) void k_attn_gather(AttnParams a, float qscale) {
-    constexpr int KB = 128 / D;        // 16-key halves of a tile
+__global__ __launch_bounds__(64, D == 64 ? 4 : 3) void k_attn_gather(AttnParams a, float qscale) {
     constexpr int SL = D / 16;         // 16-dim slices of the score product
     constexpr int DX = D / 64;         // 64-dim pieces of the output
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;
     const int li = lane & 15, lg = lane >> 4;
     const int64_t N = a.N;
-    const int64_t f = (int64_t)blockIdx.x * kFWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (f >= (int64_t)a.Hkv * N) return;
+    const int64_t f = blockIdx.x;
     const int64_t q = N - 1 - f / a.Hkv;              // heavy rows first
     const int g = (int)(f % a.Hkv);
     if (tile_is_dense(a, g, q - q % kTileRows)) return;   // that tile runs on the tiled kernel
@@ -77,73 +76,51 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void k_attn_gather(AttnParams a, f
     for (int x = 0; x < 4 * DX; ++x) o[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
 
-    f32x4_t kr[KB][SL], vr[KB][4][DX];
-    int jn[KB];                        // the loaded keys (slot 16 kb + l%16); -1: none
-    auto load_keys = [&](int64_t v0) {
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            const int64_t v = v0 + 16 * kb + li;
-            const int j = v < L ? idx[v] : -1;
-            jn[kb] = (uint32_t)j < (uint32_t)N ? j : -1;   // an index outside [0, N) is ignored
-        }
+    f32x4_t kr[SL], vr[4][DX];
+    int jn;                            // the loaded key (slot l%16); -1: none
+    auto load_key = [&](int64_t v0) {
+        const int64_t v = v0 + li;
+        const int j = v < L ? idx[v] : -1;
+        jn = (uint32_t)j < (uint32_t)N ? j : -1;       // an index outside [0, N) is ignored
     };
     auto load_k = [&]() {
+        const float* kp = Kg + (int64_t)(jn < 0 ? 0 : jn) * D + 4 * lg;   // row 0 always exists
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            const float* kp = Kg + (int64_t)(jn[kb] < 0 ? 0 : jn[kb]) * D + 4 * lg;   // row 0 always exists
+        for (int s = 0; s < SL; ++s) kr[s] = *reinterpret_cast<const f32x4_t*>(kp + 16 * s);
+    };
+    auto load_v = [&](int j) {
 #pragma unroll
-            for (int s = 0; s < SL; ++s) kr[kb][s] = *reinterpret_cast<const f32x4_t*>(kp + 16 * s);
+        for (int i = 0; i < 4; ++i) {
+            const int jv = __shfl(j, 4 * lg + i);
+            const float* vp = Vg + (int64_t)(jv < 0 ? 0 : jv) * D + 4 * li;
+#pragma unroll
+            for (int x = 0; x < DX; ++x) vr[i][x] = *reinterpret_cast<const f32x4_t*>(vp + 64 * x);
         }
     };
-    auto load_v = [&](const int (&j)[KB]) {
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int jv = __shfl(j[kb], 4 * lg + i);
-                const float* vp = Vg + (int64_t)(jv < 0 ? 0 : jv) * D + 4 * li;
-#pragma unroll
-                for (int x = 0; x < DX; ++x) {
-                    vr[kb][i][x] = *reinterpret_cast<const f32x4_t*>(vp + 64 * x);
-                }
-            }
-    };
     if (L > 0) {
-        load_keys(0);
+        load_key(0);
         load_k();
         load_v(jn);
-        for (int64_t v0 = 0; v0 < L; v0 += 16 * KB) {
-            int j[KB];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) j[kb] = jn[kb];
-            if (v0 + 16 * KB < L) load_keys(v0 + 16 * KB);
+        for (int64_t v0 = 0; v0 < L; v0 += 16) {
+            const int j = jn;
+            if (v0 + 16 < L) load_key(v0 + 16);
 
-            // S^T: lane l holds head l%16 at key slots 16 kb + 4 (l/16) + i
-            f32x4_t st[KB];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) st[kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            // S^T: lane l holds head l%16 at key slots 4 (l/16) + i
+            f32x4_t st = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < SL; ++s)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int kb = 0; kb < KB; ++kb)
-                        st[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[kb][s][e], qf[s][e], st[kb], 0, 0, 0);
-            if (v0 + 16 * KB < L) load_k();
+                    st = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[s][e], qf[s][e], st, 0, 0, 0);
+            if (v0 + 16 < L) load_k();
 
             // one online softmax step (scores in the log2 domain)
+            const uint32_t ok = (uint32_t)(__ballot(j >= 0) & 0xFFFFull);   // the tile's valid slots
             float mx = -INFINITY;
-            uint32_t ok[KB];           // the half's valid slots
-            bool whole = true;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                ok[kb] = (uint32_t)(__ballot(j[kb] >= 0) & 0xFFFFull);
-                whole = whole && ok[kb] == 0xFFFFu;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (!((ok[kb] >> (4 * lg + i)) & 1u)) st[kb][i] = -INFINITY;
-                    mx = fmaxf(mx, st[kb][i]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                if (!((ok >> (4 * lg + i)) & 1u)) st[i] = -INFINITY;
+                mx = fmaxf(mx, st[i]);
             }
             const float m_new = fmaxf(m_run, quad_max16(mx));
             // No valid entry yet: a finite stand-in keeps the weights and the
@@ -153,12 +130,10 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void k_attn_gather(AttnParams a, f
             const float alpha = exp2f(m_run - mc);
             float ps = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    st[kb][i] = exp2f(st[kb][i] - mc);
-                    ps += st[kb][i];
-                }
+            for (int i = 0; i < 4; ++i) {
+                st[i] = exp2f(st[i] - mc);
+                ps += st[i];
+            }
             l_run = l_run * alpha + ps;
             if (__ballot(m_new != m_run) != 0ull) {           // some head's max moved (or is NaN)
 #pragma unroll
@@ -171,27 +146,22 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void k_attn_gather(AttnParams a, f
             m_run = m_new;
             // Slots without a key carry weight 0; their rows must not bring in
             // another row's infinities.
-            if (!whole) {
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (!((ok[kb] >> (4 * lg + i)) & 1u)) {
-#pragma unroll
-                            for (int x = 0; x < DX; ++x) vr[kb][i][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                        }
-            }
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+            if (ok != 0xFFFFu) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
+                    if (!((ok >> (4 * lg + i)) & 1u)) {
 #pragma unroll
-                    for (int x = 0; x < DX; ++x)
+                        for (int x = 0; x < DX; ++x) vr[i][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            o[4 * x + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[kb][i], vr[kb][i][x][e], o[4 * x + e],
-                                                                              0, 0, 0);
-            if (v0 + 16 * KB < L) load_v(jn);
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int x = 0; x < DX; ++x)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        o[4 * x + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[i], vr[i][x][e], o[4 * x + e], 0, 0, 0);
+            if (v0 + 16 < L) load_v(jn);
         }
     }
 
@@ -412,7 +382,7 @@ hipError_t launch_attn_gather(const AttnParams& a, hipStream_t st) {
         else hipLaunchKernelGGL((k_attn_gather16<64>), grid, block, 0, st, a, qscale);
         return hipGetLastError();
     }
-    const dim3 grid((unsigned)(((int64_t)a.Hkv * a.N + kFWaves - 1) / kFWaves)), block(64 * kFWaves);
+    const dim3 grid((unsigned)((int64_t)a.Hkv * a.N)), block(64);
     if (a.D == 128) hipLaunchKernelGGL((k_attn_gather<128>), grid, block, 0, st, a, qscale);
     else hipLaunchKernelGGL((k_attn_gather<64>), grid, block, 0, st, a, qscale);
     return hipGetLastError();

@@ -334,9 +334,9 @@ def test_gather_ignores_indices_outside_the_sequence(dtype):
 @pytest.mark.parametrize("G", [1, 5, 8])
 @pytest.mark.parametrize("D", [64, 128])
 def test_f32_gather_tile_edges(D, G):
-    """Row lengths 0..70 (ends of 16- and 32-key tiles, and of tiles after
-    them) in float32, with a key that no row holds carrying infinities: slots
-    past a row's end must not bring it in.  Bar: 1e-5, the float32 bar."""
+    """Row lengths 0..70 (ends of 16-key tiles, and of tiles after them) in
+    float32, with a key that no row holds carrying infinities: slots past a
+    row's end must not bring it in.  Bar: 1e-5, the float32 bar."""
     from oracle import attention as o_att
     ris = need_gpu()
     Hkv, N = 2, 71
