@@ -1021,9 +1021,23 @@ hipError_t run_mask_chunk(const MaskParams& p, int64_t* row_ptr, int32_t* col_id
     return strip_status(row_ptr, rows, chunks, kRows, st);
 }
 
-// Two-phase build: waves for light rows.
+// Two-phase build: waves for light rows, where there are enough of them.  A wave
+// takes about 2.5 ns a draw where a workgroup takes 0.7, and some 6 us more per
+// further batch of seeds, but waves end a row in half the time where rows queue
+// (2 against 4 ns each): they pay from about as many rows as the last row has
+// draws, and 4,000 more per batch.  Count phase: 512 rows of 8,190 draws 16.3 us
+// by workgroups, 31 by waves, 32,768 rows to that length 290 against 205; 1,400
+// rows of 70 seeds to 490 draws 18.9 against 22.0, 8,192 to 2,870 61 against 51.
+// Structural rows differ within a block, and the heaviest wave ends the launch:
+// twice the rows (4,096 rows of 30 seeds at 5%, block 205: 26.5 against 33.6), and
+// seven times where a row's share does not fill its block, so that most rows draw
+// little (8,192 rows of 70 seeds at 1%, block 128: 26.7 against 39.1).
 bool two_phase_waves(const MaskParams& p) {
-    return middle_draws(p) < kWaveDraws && group_smem_bytes<64>(p, kThreads / 64) <= kWaveSmemTwoPhase;
+    if (middle_draws(p) >= kWaveDraws || group_smem_bytes<64>(p, kThreads / 64) > kWaveSmemTwoPhase) return false;
+    const int64_t last = row_count(p.ppm, p.causal ? p.q0 + p.nq : p.N);
+    const int64_t batches = (p.n_seeds + kSeedBatch<64> - 1) / kSeedBatch<64>;
+    const int64_t uneven = p.mode == 0 ? 1 : p.block <= last ? 2 : 7;
+    return (int64_t)p.heads * p.nq >= uneven * (p.n_seeds * last + 4000 * (batches - 1));
 }
 
 }  // namespace
