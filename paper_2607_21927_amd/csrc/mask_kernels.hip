@@ -971,6 +971,16 @@ constexpr size_t kChunk8Smem = 80 << 10;
 // against 2.07 ms, 150,000 4.36 against 3.39.
 constexpr size_t kWaveSmem = 80 << 10;
 constexpr size_t kWaveSmemTwoPhase = 64 << 10;
+// A wave takes its seeds in batches of 64, each with Philox evaluations and a walk
+// of its own, which too few rows do not hide.  Builds of 16 batches and more (960
+// seeds) with fewer than 550 rows a batch go to the persistent grid, and those of
+// 8 and more with fewer than 1,024 rows: one draw a seed, 1,000 seeds, 1,400 rows
+// 61 against 108 us, 8,192 rows 166 against 185, 32,768 rows (waves) 501; 700
+// seeds, 600 rows 34 against 41, 1,400 rows (waves) 44 against 54.  Stochastic
+// mode only: a Structural row whose share does not fill its block draws nothing.
+bool few_rows_for_waves(const MaskParams& p, int64_t rows, int64_t batches) {
+    return p.mode == 0 && ((batches >= 16 && rows < 550 * batches) || (batches >= 8 && rows < 1024));
+}
 // A dispatch holds fewer than 2^32 work-items, and a wave to a row takes 64 a row
 // (in chunks of up to 8 rows): builds of more rows go to the persistent grid,
 // whose size does not grow with them.
@@ -987,6 +997,8 @@ hipError_t fused_occupancy(const MaskParams& p, int* blocks) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_mask_fused<kDepth>, kThreads,
                                                         mask_smem_bytes(p, kDepth + 1));
 }
+
+int64_t seed_batches(const MaskParams& p) { return (p.n_seeds + kSeedBatch<64> - 1) / kSeedBatch<64>; }
 
 // Expected draws of the middle row.
 int64_t middle_draws(const MaskParams& p) {
@@ -1035,9 +1047,8 @@ hipError_t run_mask_chunk(const MaskParams& p, int64_t* row_ptr, int32_t* col_id
 bool two_phase_waves(const MaskParams& p) {
     if (middle_draws(p) >= kWaveDraws || group_smem_bytes<64>(p, kThreads / 64) > kWaveSmemTwoPhase) return false;
     const int64_t last = row_count(p.ppm, p.causal ? p.q0 + p.nq : p.N);
-    const int64_t batches = (p.n_seeds + kSeedBatch<64> - 1) / kSeedBatch<64>;
     const int64_t uneven = p.mode == 0 ? 1 : p.block <= last ? 2 : 7;
-    return (int64_t)p.heads * p.nq >= uneven * (p.n_seeds * last + 4000 * (batches - 1));
+    return (int64_t)p.heads * p.nq >= uneven * (p.n_seeds * last + 4000 * (seed_batches(p) - 1));
 }
 
 }  // namespace
@@ -1063,7 +1074,8 @@ hipError_t launch_mask_fused(const MaskParams& p, int64_t* row_ptr, int32_t* col
     const int64_t rows = (int64_t)p.heads * p.nq, draws = middle_draws(p);
     if (rows <= kFewRows && draws >= kFewRowsDraws)
         return run_mask_chunk<1024, 1>(p, row_ptr, col_idx, capacity, st);
-    if (draws < kWaveDraws && rows <= kWaveRows && group_smem_bytes<64>(p, 4) <= kWaveSmem) {
+    if (draws < kWaveDraws && rows <= kWaveRows && group_smem_bytes<64>(p, 4) <= kWaveSmem &&
+        !few_rows_for_waves(p, rows, seed_batches(p))) {
         if (draws < kChunk8Draws && group_smem_bytes<64>(p, 8) <= kChunk8Smem)
             return run_mask_chunk<64, 8>(p, row_ptr, col_idx, capacity, st);
         return run_mask_chunk<64, 4>(p, row_ptr, col_idx, capacity, st);

@@ -260,6 +260,8 @@ DISPATCH = [
     (0, 50_000, 2001, 1, 100, 0, 0, 0, 0, 2001),        # 5,000 draws: 4 waves, a last chunk of one row
     (0, 1_000, 5001, 1, 100, 0, 0, 0, 0, 5001),         # 4,500 rows and more: waves in two phases, two batches
     (0, 1_000, 5001, 1, 100, 0, 0, 0, 502, 4499),       # fewer: workgroups in two phases
+    (0, 1, 1100, 1, 500, 0, 0, 0, 76, 1024),            # eight batches of seeds on 1,024 rows: 8 waves
+    (0, 1, 1100, 1, 500, 0, 0, 0, 77, 1023),            # on fewer: the persistent grid
     (0, 100_000, 1500, 1, 130, 0, 0, 0, 0, 1500),       # 9,750 draws: the persistent grid, two rows in flight
     (0, 1_000, 80000, 1, 125, 0, 0, 0, 79400, 600),     # 10,000 draws, 80,000 keys: one row in flight
     (0, 1_000, 150000, 1, 65, 0, 0, 0, 149400, 600),    # 9,750 draws, 150,000 keys: none in flight
