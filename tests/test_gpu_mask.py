@@ -258,8 +258,10 @@ DISPATCH = [
     (0, 100_000, 512, 1, 4, 0, 0, 0, 0, 512),           # 512 rows, 104 draws: 8 waves
     (1, 50_000, 2000, 1, 100, 64, 33, 4, 0, 2000),      # two seed batches of 50 to a wave, 8 waves
     (0, 50_000, 2001, 1, 100, 0, 0, 0, 0, 2001),        # 5,000 draws: 4 waves, a last chunk of one row
-    (0, 1_000, 5001, 1, 100, 0, 0, 0, 0, 5001),         # 4,500 rows and more: waves in two phases, two batches
-    (0, 1_000, 5001, 1, 100, 0, 0, 0, 502, 4499),       # fewer: workgroups in two phases
+    (0, 1_000, 5001, 1, 100, 0, 0, 0, 0, 5001),         # rows enough for waves in two phases, two batches of seeds
+    (0, 1_000, 5001, 1, 100, 0, 0, 0, 1801, 3200),      # fewer: workgroups in two phases
+    (1, 20_000, 3000, 2, 30, 64, 0, 0, 0, 3000),        # Structural, uneven rows: waves in two phases
+    (1, 10_000, 3000, 2, 70, 128, 0, 0, 0, 3000),       # most rows draw nothing: workgroups in two phases
     (0, 1, 1100, 1, 500, 0, 0, 0, 76, 1024),            # eight batches of seeds on 1,024 rows: 8 waves
     (0, 1, 1100, 1, 500, 0, 0, 0, 77, 1023),            # on fewer: the persistent grid
     (0, 100_000, 1500, 1, 130, 0, 0, 0, 0, 1500),       # 9,750 draws: the persistent grid, two rows in flight
