@@ -222,18 +222,20 @@ __global__ void k_swiglu(const void* gu, void* out, int64_t rows, int64_t inter,
 }
 
 
-// Whole, aligned 16-byte vectors: a lane takes kSwigluVecs of them, a workgroup
-// apart so that every access of a wave is one contiguous piece.  HBM-bound:
-// 32,768 rows of 2 x 8,960 bf16 take 352 us (5.0 TB/s, the rate of a device
-// copy) against 781 us with 2-byte accesses, and 320 us past the caches.
-constexpr int kSwigluVecs = 2;
+// Whole, aligned 16-byte vectors: two a lane, a workgroup apart so that every
+// access of a wave is one contiguous piece, where a tensor goes past the caches:
+// HBM-bound, 32,768 rows of 2 x 8,960 bf16 take 286 us (6.2 TB/s) against 770 us
+// with 2-byte accesses.  Elsewhere one a lane: small tensors are one latency, which
+// two made longer than 2-byte accesses did (32 rows 3.6 us, 3.3 element by element,
+// 3.1 here; 2,048 rows 23.4, 47 and 19.6).
+constexpr int swiglu_vecs(bool stream) { return stream ? 2 : 1; }
 template <bool BF16, bool STREAM>
 __global__ __launch_bounds__(256) void k_swiglu_vec(const u32x4_t* gu, u32x4_t* out, uint32_t n, uint32_t vpr) {
-    constexpr int kVec = kVecElts<BF16>;
-    const uint32_t i0 = blockIdx.x * (256u * kSwigluVecs) + threadIdx.x;
-    u32x4_t gv[kSwigluVecs], uv[kSwigluVecs];
+    constexpr int kVec = kVecElts<BF16>, kVecs = swiglu_vecs(STREAM);
+    const uint32_t i0 = blockIdx.x * (256u * kVecs) + threadIdx.x;
+    u32x4_t gv[kVecs], uv[kVecs];
 #pragma unroll
-    for (int k = 0; k < kSwigluVecs; ++k) {
+    for (int k = 0; k < kVecs; ++k) {
         const uint32_t i = i0 + 256u * k;
         if (i < n) {
             const int64_t at = (int64_t)(i / vpr) * vpr + i;      // row 2 vpr + column
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(256) void k_swiglu_vec(const u32x4_t* gu, u32x4_t* 
         }
     }
 #pragma unroll
-    for (int k = 0; k < kSwigluVecs; ++k) {
+    for (int k = 0; k < kVecs; ++k) {
         const uint32_t i = i0 + 256u * k;
         if (i < n) {
             float g[kVec], u[kVec];
@@ -290,11 +292,20 @@ bool rmsnorm_vec(const void* x, void* residual, const void* w, void* out, int64_
     return true;
 }
 
-// Bytes read and written from which they go past the caches: twice the
-// last-level cache (256 MB), so that what the next layer reads is not in it
-// anyway.  32,768 rows of 2 x 8,960 bf16 (1.8 GB): 352 against 320 us (loads or
-// stores alone so: no gain).
+// Bytes read and written from which they go past the caches.  At 2 x 8,960 bf16,
+// the product that reads the output included: 6,000 rows (323 MB in all) 207 us in
+// the caches and 209 past them, 9,000 (484 MB) 268 and 268, 12,000 (645 MB; the
+// output alone would still fit the 256 MB last-level cache) 410 and 407, 14,000 456
+// and 451, 32,768 926 and 928; the kernel alone 54 and 55, 85 and 81, 111 and 106,
+// 129 and 124, 301 and 293.  (Loads or stores alone so: no gain.)
 constexpr int64_t kStreamBytes = 512ll << 20;
+
+template <bool BF16, bool STREAM>
+void run_swiglu_vec(const void* gu, void* out, int64_t n, int64_t vpr, hipStream_t st) {
+    constexpr int64_t kPer = 256 * swiglu_vecs(STREAM);
+    hipLaunchKernelGGL((k_swiglu_vec<BF16, STREAM>), dim3((unsigned)((n + kPer - 1) / kPer)), dim3(256), 0, st,
+                       static_cast<const u32x4_t*>(gu), static_cast<u32x4_t*>(out), (uint32_t)n, (uint32_t)vpr);
+}
 
 template <bool BF16>
 bool swiglu_vec(const void* gu, void* out, int64_t rows, int64_t inter, hipStream_t st) {
@@ -302,15 +313,8 @@ bool swiglu_vec(const void* gu, void* out, int64_t rows, int64_t inter, hipStrea
     if (inter % kVec != 0 || !aligned16(gu) || !aligned16(out)) return false;
     const int64_t vpr = inter / kVec, n = rows * vpr;
     if (n > 0x7FFFFFFFll) return false;               // 32-bit vector indices
-    const int64_t per = 256 * kSwigluVecs;
-    const dim3 grid((unsigned)((n + per - 1) / per));
-    const u32x4_t* g = static_cast<const u32x4_t*>(gu);
-    if (48 * n > kStreamBytes)
-        hipLaunchKernelGGL((k_swiglu_vec<BF16, true>), grid, dim3(256), 0, st, g, static_cast<u32x4_t*>(out),
-                           (uint32_t)n, (uint32_t)vpr);
-    else
-        hipLaunchKernelGGL((k_swiglu_vec<BF16, false>), grid, dim3(256), 0, st, g, static_cast<u32x4_t*>(out),
-                           (uint32_t)n, (uint32_t)vpr);
+    if (48 * n > kStreamBytes) run_swiglu_vec<BF16, true>(gu, out, n, vpr, st);
+    else run_swiglu_vec<BF16, false>(gu, out, n, vpr, st);
     return true;
 }
 
