@@ -87,6 +87,13 @@ __device__ __forceinline__ void load_tile(const RowSegs& r, const uint16_t* Kr, 
     T.valid = vm;
 }
 
+__device__ __forceinline__ void store_out(const DecodeParams& p, int64_t at, float y) {
+    if (p.out_bf16)
+        static_cast<uint16_t*>(p.out)[at] = f32_to_bf16(y);
+    else
+        static_cast<float*>(p.out)[at] = y;
+}
+
 template <int D, bool STREAM>
 __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeParams p, float c) {
     constexpr int SL = D / 32;         // k-slices of the score product
@@ -253,6 +260,10 @@ __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_decode_partial(DecodeP
             O += c * ow[w * G * D + e];
             L += c * ml[w][h].y;
         }
+        if (gridDim.x == 1) {                                // the row's only partial: its output
+            store_out(p, (int64_t)row * G * D + e, L > 0.f ? (O + 0.f) / L : 0.f);
+            continue;
+        }
         po[e] = O;
         if (e % D == 0) {
             pml[2 * h] = M;
@@ -313,18 +324,23 @@ __global__ __launch_bounds__(kCombineThreads) void k_decode_combine(DecodeParams
         for (int k = 0; k < kGroups; ++k) y += osum[k][tid];
         y = L > 0.f ? y / L : 0.f;
         const int64_t at = bh * D + tid;
-        if (p.out_bf16)
-            static_cast<uint16_t*>(p.out)[at] = f32_to_bf16(y);
-        else
-            static_cast<float*>(p.out)[at] = y;
+        store_out(p, at, y);
     }
 }
 
 // K and V bytes of a step from which V is read past the caches (non-temporal
 // loads of whole rows; K's 64-byte pieces need the cache for a row's other
-// pieces).  A step of more than the last-level cache holds (256 MB) finds nothing
-// of it there: 32 sequences at 64k, 1.1 GB, 188 against 170 us; one sequence, 35
-// MB that a following step may still find, 16.7 against 17.0 us.
+// pieces).  The bytes are an estimate from the descriptor, and an upper one: an
+// anchor's capacity counts every draw, and window and initial tokens may lie in it
+// (70 seeds at 1% of 64k, window 1,024: 48 MB a sequence for 33 MB read).
+// Measured in the caches / past them, 12/2 heads of 128, each step with the caches
+// full of other data, as between a model's layers: 4 sequences (192 MB by the
+// estimate) 135 / 129 us with the fill, 5 (240) 156 / 146, 6 (288) 166 / 156, 8
+// (384) 175 / 160, 12 (575) 232 / 221; the same step over and over: 31.0 / 31.4,
+// 44.2 / 46.0, 51.6 / 51.9, 50.6 / 50.6, 108 / 92, 32 sequences 201 / 182.  32/4 heads
+// of 64, over and over: 5 sequences 34.2 / 37.3, 6 40.3 / 43.2, 7 47.9 / 48.9, 8
+// 54.6 / 53.1, 12 92 / 78; with other data 147 / 138, 158 / 148, 169 / 156, 174 / 160,
+// 212 / 200.  The line lies where the repeated step loses little any more.
 constexpr int64_t kStreamBytes = 256ll << 20;
 
 template <int D>
@@ -336,7 +352,10 @@ hipError_t launch_d(const DecodeParams& p, float c, hipStream_t st) {
     else
         hipLaunchKernelGGL((k_decode_partial<D, false>), grid, dim3(64 * kDecodeWaves), 0, st, p, c);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // One partial a row is the row's output.  (Short rows: 8/8 heads of 64, 110 keys,
+    // one sequence 6.6 us with one thread per dim merging four partials, 6.9 with
+    // the merge above and this launch, 4.3 without.)
+    if (e != hipSuccess || grid.x == 1) return e;
     hipLaunchKernelGGL(k_decode_combine<D>, dim3((unsigned)((int64_t)p.B * p.Hq)), dim3(kCombineThreads), 0, st, p,
                        p.parts / kDecodeWaves);
     return hipGetLastError();
