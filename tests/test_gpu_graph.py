@@ -13,10 +13,13 @@ from synth import gaussian_qkv, to_bf16
 pytestmark = pytest.mark.gpu
 
 
-def test_hot_path_step_replays_from_a_graph():
+# By the form of the one-pass build: 8 waves (750 chunks, folded strip; 1,125
+# chunks, strip kernel), 1,024 lanes to a row, the persistent grid.
+@pytest.mark.parametrize("N,ppm,S", [(3000, 20_000, 10), (4500, 20_000, 10), (256, 100_000, 30), (3000, 100_000, 64)])
+def test_hot_path_step_replays_from_a_graph(N, ppm, S):
     ris = need_gpu()
-    Hq, Hkv, N, D, ppm, S = 12, 2, 3000, 128, 20_000, 10
-    say(f"graph capture Hq={Hq} Hkv={Hkv} N={N} D={D}")
+    Hq, Hkv, D = 12, 2, 128
+    say(f"graph capture Hq={Hq} Hkv={Hkv} N={N} D={D} {ppm} ppm x {S} seeds")
     Q, K, V = gaussian_qkv(Hq, Hkv, N, D, seed=5)
     q0, k0, v = to_bf16(Q).cuda(), to_bf16(K).cuda(), to_bf16(V).cuda()
     q, k = torch.empty_like(q0), torch.empty_like(k0)

@@ -180,26 +180,46 @@ def test_union_size_matches_its_expectation(name):
     assert abs(nnz - mean) < 5 * sd, (nnz, mean, sd)
 
 
-def _give_up_case(ris, monkeypatch, env, value, must_poison):
+# One build per form of the one-pass build, by its shape: mode, ppm, N, heads,
+# S, q_begin, q_count.
+GIVE_UP = {
+    "8 waves, strip kernel": (0, 10_000, 16384, 2, 3, 0, 16384),             # 4,096 chunks
+    "8 waves, folded strip": (0, 10_000, 4001, 2, 10, 0, 4001),              # 1,001 chunks, the last of two rows
+    "4 waves, strip kernel": (0, 50_000, 2100, 2, 100, 0, 2100),             # 1,050 chunks
+    "4 waves, folded strip": (0, 50_000, 2001, 1, 100, 0, 2001),             # 501 chunks, the last of one row
+    "1,024 lanes": (0, 10_000, 4097, 2, 70, 3841, 256),                      # 512 rows, folded
+    "persistent, two rows wait": (0, 100_000, 1500, 1, 130, 0, 1500),
+    "persistent, one row waits": (0, 1_000, 80000, 1, 125, 79400, 600),
+    "persistent, none waits": (0, 1_000, 150000, 1, 65, 149400, 600),
+}
+_give_up_want = {}
+
+
+def _give_up_case(ris, monkeypatch, form, env, value, must_poison):
     """Build with a give-up forced from the host (env=value), then check the
     reported result: nothing written past col_idx's capacity; if any row is
     poisoned, the total is -1, the binding's check raises, and every row that
     was not poisoned holds exactly the oracle's keys at its offset.  A build
     with the normal bound afterwards is exact."""
-    sp = spec_of(0, 10_000, 16384, 2, 3)
-    want_rp, want_ci = o_geo.build_csr(sp)
+    mode, ppm, N, heads, S, q0, nq = GIVE_UP[form]
+    sp = spec_of(mode, ppm, N, heads, S)
+    if form not in _give_up_want:
+        rows = [w for h in range(heads) for w in o_geo.row_sets(sp, h, np.arange(q0, q0 + nq))]
+        _give_up_want[form] = np.concatenate([[0], np.cumsum([len(w) for w in rows])]), np.concatenate(rows)
+    want_rp, want_ci = _give_up_want[form]
     d = desc_of(ris, sp)
-    cap = ris.mask_nnz_bound(d)
+    cap = ris.mask_rows_nnz_bound(d, q0, nq)
     guard = 4096
-    R = sp.heads * sp.N
+    R = heads * nq
     rp = torch.empty(R + 1, dtype=torch.int64, device="cuda")
     ci = torch.full((cap + guard,), -7, dtype=torch.int32, device="cuda")
     monkeypatch.setenv(env, str(value))
-    ris.mask_build(d, rp, ci, col_capacity=cap)
+    ris.mask_build_rows(d, q0, nq, rp, ci, col_capacity=cap)
     torch.cuda.synchronize()
     monkeypatch.delenv(env)
     rp_h, ci_h = rp.cpu().numpy(), ci.cpu().numpy()
     assert (ci_h[cap:] == -7).all(), "write past the capacity"
+    assert rp_h[0] == 0
     counts = np.diff(want_rp)
     poisoned = np.flatnonzero(rp_h[1:] < 0)
     say(f"  total {rp_h[-1]}, {len(poisoned)} of {R} rows poisoned")
@@ -221,31 +241,35 @@ def _give_up_case(ris, monkeypatch, env, value, must_poison):
         for i in range(0, len(good), max(1, len(good) // 200)):
             r, e = good[i], ends[i]
             assert np.array_equal(ci_h[e - counts[r]:e], want_ci[want_rp[r]:want_rp[r + 1]]), r
-    rp2, ci2 = gpu_csr(ris, sp, use_bound=True)
-    assert np.array_equal(rp2.cpu().numpy(), want_rp)
-    assert np.array_equal(ci2.cpu().numpy()[: want_rp[-1]], want_ci)
+    ris.mask_build_rows(d, q0, nq, rp, ci, col_capacity=cap)
+    assert np.array_equal(rp.cpu().numpy(), want_rp)
+    assert np.array_equal(ci.cpu().numpy()[: want_rp[-1]], want_ci)
     return rp_h, poisoned
 
 
-def test_lookback_give_up_is_reported(monkeypatch):
+@pytest.mark.parametrize("form", GIVE_UP)
+def test_lookback_give_up_is_reported(monkeypatch, form):
     """The one-pass build's bounded wait, forced to give up from the host
     (RIS_DEBUG_LOOKBACK_SPINS=0: a row that finds a predecessor not ready
     gives up at once, so every kernel exits normally).  Whether any row has
     to wait depends on the timing; the reported result must be right either
     way."""
     ris = need_gpu()
-    say("look-back give-up: N=16384 heads=2 S=3, spin limit 0")
-    _give_up_case(ris, monkeypatch, "RIS_DEBUG_LOOKBACK_SPINS", 0, must_poison=False)
+    say(f"look-back give-up, {form}: spin limit 0")
+    _give_up_case(ris, monkeypatch, form, "RIS_DEBUG_LOOKBACK_SPINS", 0, must_poison=False)
 
 
-def test_forced_poison_row_is_reported(monkeypatch):
+@pytest.mark.parametrize("where", ["middle", "last"])
+@pytest.mark.parametrize("form", GIVE_UP)
+def test_forced_poison_row_is_reported(monkeypatch, form, where):
     """The poison path whatever the timing: RIS_DEBUG_POISON_ROW makes one
     row publish poison in place of its look-back.  That row and the total
     must read -1, and the rest must be as above."""
     ris = need_gpu()
-    r = 2 * 16384 // 3
-    say(f"forced poison: N=16384 heads=2 S=3, row {r}")
-    rp_h, poisoned = _give_up_case(ris, monkeypatch, "RIS_DEBUG_POISON_ROW", r, must_poison=True)
+    R = GIVE_UP[form][3] * GIVE_UP[form][6]
+    r = R - 1 if where == "last" else R // 3
+    say(f"forced poison, {form}: row {r} of {R}")
+    rp_h, poisoned = _give_up_case(ris, monkeypatch, form, "RIS_DEBUG_POISON_ROW", r, must_poison=True)
     assert rp_h[r + 1] == -1 and r in poisoned
     assert (rp_h[1:r + 1] >= 0).all(), "a row before the poisoned one was poisoned"
 
@@ -256,6 +280,8 @@ DISPATCH = [
     (0, 10_000, 4097, 2, 70, 0, 0, 0, 3841, 256),       # 512 rows, 2,800 draws: 1,024 lanes to a row
     (0, 10_000, 4097, 2, 70, 0, 0, 0, 3840, 257),       # 514 rows: 8 waves, a last chunk of two rows
     (0, 100_000, 512, 1, 4, 0, 0, 0, 0, 512),           # 512 rows, 104 draws: 8 waves
+    (0, 10_000, 8192, 1, 3, 0, 0, 0, 0, 8192),          # 1,024 chunks: the last workgroup strips the statuses
+    (0, 10_000, 8193, 1, 3, 0, 0, 0, 0, 8193),          # 1,025: the strip kernel does
     (1, 50_000, 2000, 1, 100, 64, 33, 4, 0, 2000),      # two seed batches of 50 to a wave, 8 waves
     (0, 50_000, 2001, 1, 100, 0, 0, 0, 0, 2001),        # 5,000 draws: 4 waves, a last chunk of one row
     (0, 1_000, 5001, 1, 100, 0, 0, 0, 0, 5001),         # rows enough for waves in two phases, two batches of seeds
