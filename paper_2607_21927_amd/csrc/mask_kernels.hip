@@ -342,11 +342,6 @@ __device__ __forceinline__ uint32_t range_bits(uint32_t w, uint32_t lo, uint32_t
     return (n == 32u ? ~0u : ((1u << n) - 1u)) << (a - b0);
 }
 
-// Fill `bits` (W words, already visible to the whole block) with the union of
-// every seed's draws for row (h, q), on top of the local window and the
-// initial-token anchor clipped to the pool (above the pool they lie inside the
-// Structural clique, which is emitted as a range of its own).  Ends with a
-// block barrier.
 // Row words of seed s of row (h, q) into LDS.
 __device__ __forceinline__ void store_row_words(const MaskParams& p, int s, int64_t q, int h, uint32_t* dst) {
     uint32_t w[kRowWords];
@@ -355,7 +350,12 @@ __device__ __forceinline__ void store_row_words(const MaskParams& p, int s, int6
     *reinterpret_cast<u32x4_t*>(dst + 4) = u32x4_t{w[4], w[5], w[6], w[7]};
 }
 
-// With `have_words` (one batch of seeds) the row words are in rks already.
+// Fill `bits` (W words, already visible to the whole group) with the union of
+// every seed's draws for row (h, q), on top of the local window and the
+// initial-token anchor clipped to the pool (above the pool they lie inside the
+// Structural clique, which is emitted as a range of its own).  Ends with the
+// group's accesses ordered (group_sync).  With `have_words` (one batch of seeds)
+// the row words are in rks already.
 template <int T>
 __device__ void build_row_bitmap(const MaskParams& p, int64_t q, int h, const RowGeom& g,
                                  uint32_t* rks, uint32_t* bits, bool have_words = false) {
@@ -1000,7 +1000,9 @@ hipError_t fused_occupancy(const MaskParams& p, int* blocks) {
 
 int64_t seed_batches(const MaskParams& p) { return (p.n_seeds + kSeedBatch<64> - 1) / kSeedBatch<64>; }
 
-// Expected draws of the middle row.
+// Expected draws of the middle row; in Structural mode an upper bound, since the
+// clique's length comes off every row's draws (the crossovers above are those of
+// Stochastic rows).
 int64_t middle_draws(const MaskParams& p) {
     const int64_t mid = p.q0 + p.nq / 2;
     return (int64_t)p.n_seeds * row_count(p.ppm, p.causal ? mid + 1 : p.N);

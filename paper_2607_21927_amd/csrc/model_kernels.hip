@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_swiglu_vec(const u32x4_t* gu, u32x4_t* 
 
 // Rows of whole vectors, up to 8,192 bf16 or 4,096 float32 columns.  A workgroup to
 // a row has more loads in flight where rows are few (256 rows of 1,536 bf16 with
-// the residual: 2.9 against 4.6 us), 32 lanes to a row cost less where they are
+// the residual: 2.7 against 4.6 us), 32 lanes to a row cost less where they are
 // many (16,384 rows of 1,000: 20.8 against 22.6); 64 lanes gain nothing on float32
 // rows of more than two vectors a lane (16,384 of 1,536: 60.6 against 63.3).
 template <bool BF16>
