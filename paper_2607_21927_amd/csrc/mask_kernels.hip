@@ -87,7 +87,7 @@ struct RowGeom {
     uint32_t clique_len;
 };
 
-__device__ __forceinline__ RowGeom row_geometry(const MaskParams& p, int64_t q) {
+__host__ __device__ __forceinline__ RowGeom row_geometry(const MaskParams& p, int64_t q) {
     RowGeom g;
     if (p.mode == 0) {
         const int64_t n = p.causal ? q + 1 : p.N;
@@ -950,9 +950,10 @@ size_t group_smem_bytes(const MaskParams& p, int groups) {
 // Workgroups per CU below which a deeper one-pass pipeline costs more
 // occupancy than its shorter waits gain.
 constexpr int kMinResidentRows = 6;
-// Rows of fewer expected draws are built by a wave each.  A workgroup to such a
-// row spends most of its time between barriers and takes a ticket per row
-// (12.5 ns each on MI355X, whatever the row's work): 32k layers of 10 seeds
+// Rows of fewer expected draws may be built by a wave each (one_pass_form and
+// two_phase_waves say where).  A workgroup to such a row spends most of its time
+// between barriers and, in the persistent grid, takes a ticket per row (12.5 ns
+// each on MI355X, whatever the row's work): 32k layers of 10 seeds
 // (1,640 draws) 608 -> 340 us, an 8k layer of 70 (2,870) 211 -> 170, a 4k layer
 // of 10 90 -> 34; 4,900 draws 949 -> 702, 6,600 2,188 -> 1,932, 9,800 2,735 ->
 // 2,660.  From there the LDS of a bitmap per wave leaves too few waves (11,500
@@ -971,34 +972,24 @@ constexpr size_t kChunk8Smem = 80 << 10;
 // against 2.07 ms, 150,000 4.36 against 3.39.
 constexpr size_t kWaveSmem = 80 << 10;
 constexpr size_t kWaveSmemTwoPhase = 64 << 10;
-// A wave takes its seeds in batches of 64, each with Philox evaluations and a walk
-// of its own, which too few rows do not hide.  Builds of 16 batches and more (960
-// seeds) with fewer than 550 rows a batch go to the persistent grid, and those of
-// 8 and more with fewer than 1,024 rows: one draw a seed, 1,000 seeds, 1,400 rows
-// 61 against 108 us, 8,192 rows 166 against 185, 32,768 rows (waves) 501; 700
-// seeds, 600 rows 34 against 41, 1,400 rows (waves) 44 against 54.  Stochastic
-// mode only: a Structural row whose share does not fill its block draws nothing.
-bool few_rows_for_waves(const MaskParams& p, int64_t rows, int64_t batches) {
-    return p.mode == 0 && ((batches >= 16 && rows < 550 * batches) || (batches >= 8 && rows < 1024));
-}
-// A dispatch holds fewer than 2^32 work-items, and a wave to a row takes 64 a row
-// (in chunks of up to 8 rows): builds of more rows go to the persistent grid,
-// whose size does not grow with them.
-constexpr int64_t kWaveRows = (1ll << 26) - 8;
+// A dispatch holds fewer than 2^32 work-items: builds of more rows, 64 or 256 lanes
+// each (in chunks of up to 8 rows), go to the persistent grid, whose size does not
+// grow with them.
+constexpr int64_t kMaxItems = (1ll << 32) - 512;
 // Builds of at most this many rows leave CUs idle with 256 lanes to a row; 1,024
 // lanes take a row of 46,000 draws in 29 instead of 47 us (2 rows; 512 rows of
-// the same 63 instead of 75, 1,024 rows 109 against 105), and one of 655 in 13
-// instead of 22 (a wave: 19).  Rows of a few draws a lane stay with the waves.
+// the same 63 instead of 75, 1,024 rows 109 against 105).  Lighter rows gain less
+// than the larger workgroup's barriers cost, and so do rows light in each batch of
+// seeds: rows of 640 to 2,560 draws take 0.59 of the persistent grid's time with 256
+// lanes and 0.65 with 1,024, of 2,600 and more 0.69 and 0.63.
 constexpr int64_t kFewRows = 512;
-constexpr int64_t kFewRowsDraws = 256;
+constexpr double kFewRowsDraws = 4000;
 
 template <int kDepth>
 hipError_t fused_occupancy(const MaskParams& p, int* blocks) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_mask_fused<kDepth>, kThreads,
                                                         mask_smem_bytes(p, kDepth + 1));
 }
-
-int64_t seed_batches(const MaskParams& p) { return (p.n_seeds + kSeedBatch<64> - 1) / kSeedBatch<64>; }
 
 // Expected draws of the middle row; in Structural mode an upper bound, since the
 // clique's length comes off every row's draws (the crossovers above are those of
@@ -1035,6 +1026,76 @@ hipError_t run_mask_chunk(const MaskParams& p, int64_t* row_ptr, int32_t* col_id
     return strip_status(row_ptr, rows, chunks, kRows, st);
 }
 
+// A seed's draws in the build's rows: of the middle row, of the heaviest, and the
+// share of rows that draw at all.
+struct RowDraws {
+    double mean, most, share;
+};
+RowDraws row_draws(const MaskParams& p) {
+    const int64_t mid = p.q0 + p.nq / 2, last = p.q0 + p.nq - 1;
+    const int64_t k_mid = row_count(p.ppm, p.causal ? mid + 1 : p.N);
+    if (p.mode == 0) return {(double)k_mid, (double)row_count(p.ppm, p.causal ? last + 1 : p.N), 1.0};
+    // A block's rows draw k - 1, k - 2, .. keys, the clique's length less each, down
+    // to none: the heaviest is the first row or that of the last block.
+    int64_t most = row_geometry(p, p.q0).draws;
+    const int64_t start = last / p.block * p.block;
+    if (start >= p.q0 && row_geometry(p, start).draws > most) most = row_geometry(p, start).draws;
+    if (most == 0) return {0.0, 0.0, 0.0};
+    const double n = (double)(k_mid - 1 < p.block ? k_mid - 1 : p.block);
+    return {n > 0.0 ? (n * (double)k_mid - n * (n + 1.0) / 2.0) / p.block : 0.0, (double)most,
+            most < p.block ? (double)most / p.block : 1.0};
+}
+
+// What a form's build takes, in us: the heaviest row's batches of seeds one after the
+// other, each with Philox evaluations and a walk (the draws of a lane), and what the
+// rows together keep the chip with.  One-pass rows are taken head by head, light to
+// heavy, and a head's first ones wait for the offsets of the last head's heaviest.
+// Fitted to 4,800 builds of 1 to 300,000 rows, 1 to 1,200 seeds and up to 16,000 draws a
+// row, timed in every form; the predictions are off by 9 to 19% (rms).
+struct FormCost {
+    int lanes;                    // to a row
+    double base;
+    double batch, lane_draw;      // of the heaviest row: per batch, and per draw of a lane
+    double head;                  // of that, again for every further head of 8,192 rows
+    double row, first_rows;       // per 1,000 rows, and of the first 1,000
+    double row_batch, draw;       // per 1,000 (row, batch) pairs, per 64,000 draws
+    double uneven;                // by how much a Structural row counts as the heaviest, not the mean
+};
+double form_us(const MaskParams& p, const RowDraws& d, const FormCost& c) {
+    const int most_seeds = c.lanes == 64 ? kSeedBatch<64> : kSeedBatch<256>;
+    const double batches = (double)((p.n_seeds + most_seeds - 1) / most_seeds);
+    const int64_t pool = p.causal ? p.q0 + p.nq : p.N;
+    double domain = 2.0;                                          // a draw's cycle walk: domain / pool steps
+    while (domain < (double)pool) domain *= 2.0;
+    const double rounds = pool <= 128 ? 2.0 : 1.0;                // twelve rounds to a step instead of six
+    const double lane = ceil(p.n_seeds / batches) * d.most / c.lanes;
+    const double heaviest =
+        d.most > 0.0 ? batches * (c.batch + c.lane_draw * rounds * (domain / (double)pool) * (lane > 1.0 ? lane : 1.0)) : 0.0;
+    const double mean = p.mode == 0 ? d.mean : d.mean + c.uneven * (d.most - d.mean);
+    const double rows = 1e-3 * (double)p.heads * (double)p.nq;
+    return c.base + heaviest * (1.0 + c.head * (p.heads - 1) * (p.nq < 8192 ? p.nq / 8192.0 : 1.0)) +
+           rows * (c.row + c.row_batch * d.share * batches + c.draw * rounds * p.n_seeds * mean / 64.0) +
+           c.first_rows * (rows < 1.0 ? rows : 1.0);
+}
+
+// One-pass build of light rows: a wave to a row in chunks of 8 or 4, a workgroup to a
+// row in chunks of one, or the persistent grid, by the least of the three.  Rows that
+// queue are built faster by waves (32,768 rows of one draw 51 us, 300 in the grid);
+// few rows, many seeds or heavy rows end with the slowest wave (2,420 rows of 400
+// seeds, 40 draws each, 139 us by waves, 81 in the grid; 591 rows of 150 seeds to 59
+// draws 69 and 51; 8 heads of 22,781 rows of 70 seeds to 228 draws 3,890 and 3,530),
+// and the workgroups are faster than the grid where rows are few (0.6 to 0.9 of its
+// time to 2,048 rows).  Of the 4,800 builds 20 are more than 3% slower than in the
+// grid with two rows to a ticket; with waves wherever rows are light one in twenty
+// was, some by half.
+enum class OnePass { kWaves, kChunks, kGrid };
+OnePass one_pass_form(const MaskParams& p, const RowDraws& d) {
+    const double waves = 0.5 + form_us(p, d, {64, 9.0, 3.6, 0.215, 0.5, 1.8, 0.8, 0.5, 0.125, 0.15});
+    const double chunks = form_us(p, d, {256, 7.3, 3.05, 0.21, 0.27, 11.4, 8.5, 0.43, 0.064, 0.1});
+    const double grid = form_us(p, d, {256, 8.7, 3.2, 0.19, 0.0, 12.0, 18.5, 0.15, 0.047, 0.0});
+    return waves <= chunks && waves <= grid ? OnePass::kWaves : chunks <= grid ? OnePass::kChunks : OnePass::kGrid;
+}
+
 // Two-phase build: waves for light rows, where there are enough of them.  A wave
 // takes about 2.5 ns a draw where a workgroup takes 0.7, and some microseconds more
 // per further batch of seeds, but where rows queue waves end one in 2 ns instead
@@ -1061,7 +1122,7 @@ bool two_phase_waves(const MaskParams& p) {
     if (mean <= 0.0 || most <= 0.0) return true;
     const double above = most / mean - 3.0, uneven = above > 0.0 ? 1.0 + 0.2 * above : 1.0;
     return (double)p.heads * (double)p.nq * (1.0 + 2e-4 * p.n_seeds * mean) >=
-           uneven * (p.n_seeds * most + 3000.0 * (double)(seed_batches(p) - 1));
+           uneven * (p.n_seeds * most + 3000.0 * (double)((p.n_seeds - 1) / kSeedBatch<64>));
 }
 
 }  // namespace
@@ -1085,10 +1146,15 @@ hipError_t launch_mask_count(const MaskParams& p, int64_t* row_ptr, hipStream_t 
 hipError_t launch_mask_fused(const MaskParams& p, int64_t* row_ptr, int32_t* col_idx,
                              int64_t capacity, hipStream_t st) {
     const int64_t rows = (int64_t)p.heads * p.nq, draws = middle_draws(p);
-    if (rows <= kFewRows && draws >= kFewRowsDraws)
+    const RowDraws d = row_draws(p);
+    const bool light = draws < kWaveDraws && group_smem_bytes<64>(p, 4) <= kWaveSmem;
+    const double batch_draws = d.mean * (p.n_seeds < kSeedBatch<1024> ? p.n_seeds : kSeedBatch<1024>);
+    if (rows <= kFewRows && (!light || batch_draws >= kFewRowsDraws))
         return run_mask_chunk<1024, 1>(p, row_ptr, col_idx, capacity, st);
-    if (draws < kWaveDraws && rows <= kWaveRows && group_smem_bytes<64>(p, 4) <= kWaveSmem &&
-        !few_rows_for_waves(p, rows, seed_batches(p))) {
+    const OnePass form = light ? one_pass_form(p, d) : OnePass::kGrid;
+    if (form == OnePass::kChunks && rows * kThreads <= kMaxItems)
+        return run_mask_chunk<kThreads, 1>(p, row_ptr, col_idx, capacity, st);
+    if (form == OnePass::kWaves && rows * 64 <= kMaxItems) {
         if (draws < kChunk8Draws && group_smem_bytes<64>(p, 8) <= kChunk8Smem)
             return run_mask_chunk<64, 8>(p, row_ptr, col_idx, capacity, st);
         return run_mask_chunk<64, 4>(p, row_ptr, col_idx, capacity, st);

@@ -14,8 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 # By the form of the one-pass build: 8 waves (750 chunks, folded strip; 1,125
-# chunks, strip kernel), 1,024 lanes to a row, the persistent grid.
-@pytest.mark.parametrize("N,ppm,S", [(3000, 20_000, 10), (4500, 20_000, 10), (256, 100_000, 30), (3000, 100_000, 64)])
+# chunks, strip kernel), 1,024 lanes to a row, 256 lanes to a row (1,024 chunks,
+# folded strip; 1,026, strip kernel), the persistent grid.
+@pytest.mark.parametrize("N,ppm,S", [(3000, 20_000, 10), (4500, 20_000, 10), (256, 200_000, 200),
+                                     (512, 20_000, 300), (513, 20_000, 300), (3000, 100_000, 64)])
 def test_hot_path_step_replays_from_a_graph(N, ppm, S):
     ris = need_gpu()
     Hq, Hkv, D = 12, 2, 128

@@ -185,9 +185,11 @@ def test_union_size_matches_its_expectation(name):
 GIVE_UP = {
     "8 waves, strip kernel": (0, 10_000, 16384, 2, 3, 0, 16384),             # 4,096 chunks
     "8 waves, folded strip": (0, 10_000, 4001, 2, 10, 0, 4001),              # 1,001 chunks, the last of two rows
-    "4 waves, strip kernel": (0, 50_000, 2100, 2, 100, 0, 2100),             # 1,050 chunks
-    "4 waves, folded strip": (0, 50_000, 2001, 1, 100, 0, 2001),             # 501 chunks, the last of one row
-    "1,024 lanes": (0, 10_000, 4097, 2, 70, 3841, 256),                      # 512 rows, folded
+    "4 waves, strip kernel": (0, 100, 100000, 1, 3, 95000, 4101),            # 1,026 chunks, the last of one row
+    "4 waves, folded strip": (0, 100, 100000, 1, 3, 95000, 4093),            # 1,024 chunks, the last of one row
+    "256 lanes, strip kernel": (0, 5_000, 2100, 1, 300, 0, 2100),
+    "256 lanes, folded strip": (0, 1_000, 1000, 1, 600, 0, 1000),
+    "1,024 lanes": (0, 20_000, 4097, 2, 70, 3841, 256),                      # 512 rows, folded
     "persistent, two rows wait": (0, 100_000, 1500, 1, 130, 0, 1500),
     "persistent, one row waits": (0, 1_000, 80000, 1, 125, 79400, 600),
     "persistent, none waits": (0, 1_000, 150000, 1, 65, 149400, 600),
@@ -277,23 +279,30 @@ def test_forced_poison_row_is_reported(monkeypatch, form, where):
 # One row range per form of the builds, at its edges (draws: of the middle row).
 DISPATCH = [
     # mode, ppm, N, heads, S, block, window, anchor, q_begin, q_count
-    (0, 10_000, 4097, 2, 70, 0, 0, 0, 3841, 256),       # 512 rows, 2,800 draws: 1,024 lanes to a row
-    (0, 10_000, 4097, 2, 70, 0, 0, 0, 3840, 257),       # 514 rows: 8 waves, a last chunk of two rows
+    (0, 20_000, 4097, 2, 70, 0, 0, 0, 3841, 256),       # 512 rows, 5,530 draws: 1,024 lanes to a row
+    (0, 20_000, 4097, 2, 70, 0, 0, 0, 3840, 257),       # 514 rows: 256 lanes
+    (0, 10_000, 4097, 2, 70, 0, 0, 0, 3841, 256),       # 512 rows, 2,800 draws: 256 lanes
+    (0, 10_000, 4097, 2, 10, 0, 0, 0, 3840, 257),       # 400 draws: 8 waves, a last chunk of two rows
     (0, 100_000, 512, 1, 4, 0, 0, 0, 0, 512),           # 512 rows, 104 draws: 8 waves
     (0, 10_000, 8192, 1, 3, 0, 0, 0, 0, 8192),          # 1,024 chunks: the last workgroup strips the statuses
     (0, 10_000, 8193, 1, 3, 0, 0, 0, 0, 8193),          # 1,025: the strip kernel does
-    (1, 50_000, 2000, 1, 100, 64, 33, 4, 0, 2000),      # two seed batches of 50 to a wave, 8 waves
-    (0, 50_000, 2001, 1, 100, 0, 0, 0, 0, 2001),        # 5,000 draws: 4 waves, a last chunk of one row
+    (0, 20_000, 512, 2, 300, 0, 0, 0, 0, 512),          # 256 lanes, 1,024 chunks
+    (0, 20_000, 513, 2, 300, 0, 0, 0, 0, 513),          # 1,026
+    (0, 1, 1100, 1, 500, 0, 0, 0, 77, 1023),            # 256 lanes, two batches of seeds
+    (1, 50_000, 2000, 1, 100, 64, 33, 4, 0, 2000),      # Structural by 256 lanes
+    (1, 10_000, 4097, 2, 70, 64, 33, 4, 0, 4097),       # by 8 waves, two seed batches of 35 to a wave
+    (0, 100, 100000, 1, 3, 0, 0, 0, 95000, 4093),       # 100,000 keys: 4 waves, a last chunk of one row
     (0, 1_000, 5001, 1, 100, 0, 0, 0, 0, 5001),         # rows enough for waves in two phases, two batches of seeds
     (0, 1_000, 5001, 1, 100, 0, 0, 0, 1801, 3200),      # fewer: workgroups in two phases
     (1, 20_000, 3000, 2, 30, 64, 0, 0, 0, 3000),        # Structural, uneven rows: waves in two phases
     (1, 10_000, 3000, 2, 70, 128, 0, 0, 0, 3000),       # most rows draw nothing: workgroups in two phases
-    (0, 1, 1100, 1, 500, 0, 0, 0, 76, 1024),            # eight batches of seeds on 1,024 rows: 8 waves
-    (0, 1, 1100, 1, 500, 0, 0, 0, 77, 1023),            # on fewer: the persistent grid
+    (1, 20_000, 128, 2, 30, 128, 0, 0, 0, 128),         # none does: the block is as long as the sequence
+    (1, 10_000, 129, 5, 30, 64, 0, 0, 0, 129),          # none does: a clique is no shorter than the row
     (0, 100_000, 1500, 1, 130, 0, 0, 0, 0, 1500),       # 9,750 draws: the persistent grid, two rows in flight
     (0, 1_000, 80000, 1, 125, 0, 0, 0, 79400, 600),     # 10,000 draws, 80,000 keys: one row in flight
     (0, 1_000, 150000, 1, 65, 0, 0, 0, 149400, 600),    # 9,750 draws, 150,000 keys: none in flight
     (0, 1_000, 262144, 1, 2, 0, 0, 0, 261544, 600),     # light rows whose bitmaps are too large for waves
+    (0, 1_000, 262144, 1, 2, 0, 0, 0, 261644, 500),     # few of them: 1,024 lanes
 ]
 
 
