@@ -1096,33 +1096,14 @@ OnePass one_pass_form(const MaskParams& p, const RowDraws& d) {
     return waves <= chunks && waves <= grid ? OnePass::kWaves : chunks <= grid ? OnePass::kChunks : OnePass::kGrid;
 }
 
-// Two-phase build: waves for light rows, where there are enough of them.  A wave
-// takes about 2.5 ns a draw where a workgroup takes 0.7, and some microseconds more
-// per further batch of seeds, but where rows queue waves end one in 2 ns instead
-// of 4: they pay from about as many rows as the heaviest row has draws, and 3,000
-// more per batch.  Count phase: 512 rows of 8,190 draws 16.3 us by workgroups, 31
-// by waves, 32,768 rows to that length 290 and 205; 1,400 rows of 70 seeds to 490
-// draws 18.9 and 22.0, 8,192 to 2,870 61 and 51.  Structural rows differ within a
-// block, the most where their share does not fill it, and the heaviest wave ends
-// the launch: more rows are asked for the further it lies above the mean (8,192
-// rows of 70 seeds at 1%, block 128: 26.7 and 39.1; of 30 seeds at 2%, block 64: 39
-// and 32).  Of 1,198 builds timed 7 are 4 to 10% slower than by workgroups.
+// Two-phase build, likewise: 32,768 rows to 2,870 draws 205 us by waves and 290 by
+// workgroups, 512 rows of 8,190 draws 31 and 16.  Of the 4,800 count phases 10 are
+// more than 7% slower than by workgroups alone.
 bool two_phase_waves(const MaskParams& p) {
     if (middle_draws(p) >= kWaveDraws || group_smem_bytes<64>(p, kThreads / 64) > kWaveSmemTwoPhase) return false;
-    const int64_t mid = p.q0 + p.nq / 2;
-    const int64_t k_mid = row_count(p.ppm, p.causal ? mid + 1 : p.N);
-    const int64_t k_last = row_count(p.ppm, p.causal ? p.q0 + p.nq : p.N);
-    double mean = (double)k_mid, most = (double)k_last;
-    if (p.mode != 0) {
-        // a block's rows draw k - 1, k - 2, .. keys, the clique's length less each, down to none
-        const int64_t n = k_mid - 1 < p.block ? k_mid - 1 : p.block;
-        mean = (double)(n * k_mid - n * (n + 1) / 2) / p.block;
-        most -= 1.0;
-    }
-    if (mean <= 0.0 || most <= 0.0) return true;
-    const double above = most / mean - 3.0, uneven = above > 0.0 ? 1.0 + 0.2 * above : 1.0;
-    return (double)p.heads * (double)p.nq * (1.0 + 2e-4 * p.n_seeds * mean) >=
-           uneven * (p.n_seeds * most + 3000.0 * (double)((p.n_seeds - 1) / kSeedBatch<64>));
+    const RowDraws d = row_draws(p);
+    return 1.0 + form_us(p, d, {64, 4.8, 4.0, 0.12, 0.0, 0.75, 0.0, 0.85, 0.076, 0.025}) <=
+           form_us(p, d, {256, 4.8, 3.13, 0.187, 0.0, 1.1, 0.0, 2.55, 0.087, 0.0});
 }
 
 }  // namespace
