@@ -306,13 +306,17 @@ int64_t decode_keys(const ris_decode_desc& d) {
     return (d.anchor_stride + d.Hkv - 1) / d.Hkv + win + snk;
 }
 
-// Waves per row (the workspace has room for a partial of each; a workgroup's
-// waves write one together).  Any value covers every key (the tiles are dealt
-// round-robin); this one aims at ~2048 resident waves over the batch without
+// Key tiles of a typical row.
+int64_t decode_tiles(const ris_decode_desc& d) {
+    return (decode_keys(d) + ris::kDecodeTileKeys - 1) / ris::kDecodeTileKeys;
+}
+
+// Waves per row at most (the workspace has room for a partial of each; a
+// workgroup's waves write one together).  Any value covers every key (the tiles are
+// dealt round-robin); this one aims at ~2048 resident waves over the batch without
 // giving a wave less than one tile of a typical row.
 int64_t decode_parts(const ris_decode_desc& d) {
-    const int64_t keys = decode_keys(d);
-    const int64_t tiles = (keys + ris::kDecodeTileKeys - 1) / ris::kDecodeTileKeys;
+    const int64_t tiles = decode_tiles(d);
     const int64_t rows = (int64_t)d.batch * d.Hkv;
     int64_t parts = (ris::kDecodeTargetWaves + rows - 1) / rows;
     if (parts > tiles) parts = tiles;
@@ -320,6 +324,20 @@ int64_t decode_parts(const ris_decode_desc& d) {
     if (parts < ris::kDecodeWaves) parts = ris::kDecodeWaves;
     if (parts > ris::kDecodeMaxParts) parts = ris::kDecodeMaxParts;
     return parts;
+}
+
+// Waves per row.  Short rows take one workgroup whatever the batch, since the merge
+// of two in another launch costs more than a second or third tile in a wave: rows of
+// 5 to 8 tiles 5.8-7.3 us with a partial of each of eight waves, 6.1-7.6 with two
+// workgroups' partials, 4.1-5.1 with one workgroup; of 9 to 12 7.2-9.7, 6.5-8.3 and
+// 5.1-7.5; of 13 to 16 6.5, 6.7 and 6.4 at D = 64, 7.8, 7.7 and 9.0 at D = 128.
+// Where the batch leaves a row two workgroups at most, one is faster to 32 tiles
+// (256 rows and more: 16 tiles 7.9, 8.8 and 6.5 us, 32 tiles 22.0, 22.0 and 18.7).
+constexpr int64_t kSoloTiles = 12, kSoloTilesManyRows = 32;
+int64_t decode_waves(const ris_decode_desc& d) {
+    const int64_t per_row = (ris::kDecodeTargetWaves + (int64_t)d.batch * d.Hkv - 1) / ((int64_t)d.batch * d.Hkv);
+    const int64_t solo = per_row <= 2 * ris::kDecodeWaves ? kSoloTilesManyRows : kSoloTiles;
+    return decode_tiles(d) <= solo ? ris::kDecodeWaves : decode_parts(d);
 }
 
 int validate_decode(const ris_decode_desc* d) {
@@ -434,7 +452,7 @@ int ris_decode_attn(const void* Q, const void* K, const void* V, const int64_t* 
     p.B = d.batch; p.Hq = d.Hq; p.Hkv = d.Hkv; p.G = d.Hq / d.Hkv; p.D = d.D;
     p.out_bf16 = d.dtype_out == RIS_BF16;
     p.window = d.window; p.sink = d.sink;
-    p.parts = (int32_t)decode_parts(d);
+    p.parts = (int32_t)decode_waves(d);
     // a row holds max_len keys at most: no overflow for any descriptor
     const int64_t keys = decode_keys(d) < d.max_len ? decode_keys(d) : d.max_len;
     p.kv_bytes = (int64_t)d.batch * d.Hkv * keys * d.D * 4;

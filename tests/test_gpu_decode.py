@@ -148,12 +148,22 @@ def test_decode_matches_oracle(case):
 
 # Workgroup partials per row at the edges of the merge's lane groups (8 groups
 # at D = 128, 16 at D = 64): 1, 7, 8, 9, 16, 17, and the most there are (256,
-# where some waves take a second tile).
+# where some waves take a second tile); and 12 and 13 tiles, where one workgroup
+# (three tiles to a wave) gives way to four.
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("window", [1, 896, 1024, 1152, 2048, 2176, 33000])
+@pytest.mark.parametrize("window", [1, 383, 384, 896, 1024, 1152, 2048, 2176, 33000])
 def test_decode_partial_counts(window, D):
     say(f"decode partials window {window} D {D}")
     got, want, vmax = run_decode(5, 1, D, 0, 1, 1, 0, window, 0, [3], [window + 40], window + 50)
+    assert float(np.abs(got - want).max()) <= tight_tol(vmax)
+
+
+# 256 rows: one workgroup each to 32 tiles, two from there on.
+@pytest.mark.parametrize("window", [1023, 1024])
+def test_decode_many_short_rows(window):
+    say(f"decode many short rows, window {window}")
+    got, want, vmax = run_decode(2, 2, 64, 0, 1, 1, 0, window, 0, [3] * 128, [window + 9 + b for b in range(128)],
+                                 window + 140)
     assert float(np.abs(got - want).max()) <= tight_tol(vmax)
 
 
