@@ -968,10 +968,11 @@ constexpr int64_t kChunk8Draws = 4000;
 constexpr size_t kChunk8Smem = 80 << 10;
 // Pools of 160,000 keys and more (four bitmaps over 80 KB, one workgroup of four
 // waves to a CU) go to the persistent grid: 262,144 keys, 6,600 draws 8.0
-// against 13.6 ms.  The two-phase build's waves end earlier: 100,000 keys 1.94
-// against 2.07 ms, 150,000 4.36 against 3.39.
+// against 13.6 ms.  The two-phase build's waves end at 65,536 keys: further on some
+// builds gain 15% and others lose as much or more (101,000 keys, 8,184 rows of 70
+// seeds 200 us against 140; 106,000 keys, 4,376 rows of 10 seeds 33 against 27).
 constexpr size_t kWaveSmem = 80 << 10;
-constexpr size_t kWaveSmemTwoPhase = 64 << 10;
+constexpr int64_t kWaveKeysTwoPhase = 65536;
 // A dispatch holds fewer than 2^32 work-items: builds of more rows, 64 or 256 lanes
 // each (in chunks of up to 8 rows), go to the persistent grid, whose size does not
 // grow with them.
@@ -1050,8 +1051,8 @@ RowDraws row_draws(const MaskParams& p) {
 // other, each with Philox evaluations and a walk (the draws of a lane), and what the
 // rows together keep the chip with.  One-pass rows are taken head by head, light to
 // heavy, and a head's first ones wait for the offsets of the last head's heaviest.
-// Fitted to 4,800 builds of 1 to 300,000 rows, 1 to 1,200 seeds and up to 16,000 draws a
-// row, timed in every form; the predictions are off by 9 to 19% (rms).
+// Fitted to 6,000 builds of 1 to 300,000 rows, 1 to 1,200 seeds and up to 16,000 draws a
+// row, timed in every form; the predictions are off by 9 to 20% (rms).
 struct FormCost {
     int lanes;                    // to a row
     double base;
@@ -1060,6 +1061,7 @@ struct FormCost {
     double row, first_rows;       // per 1,000 rows, and of the first 1,000
     double row_batch, draw;       // per 1,000 (row, batch) pairs, per 64,000 draws
     double uneven;                // by how much a Structural row counts as the heaviest, not the mean
+    double keys;                  // of the heaviest row: per 65,536 keys of its bitmap
 };
 double form_us(const MaskParams& p, const RowDraws& d, const FormCost& c) {
     const int most_seeds = c.lanes == 64 ? kSeedBatch<64> : kSeedBatch<256>;
@@ -1069,8 +1071,8 @@ double form_us(const MaskParams& p, const RowDraws& d, const FormCost& c) {
     while (domain < (double)pool) domain *= 2.0;
     const double rounds = pool <= 128 ? 2.0 : 1.0;                // twelve rounds to a step instead of six
     const double lane = ceil(p.n_seeds / batches) * d.most / c.lanes;
-    const double heaviest =
-        d.most > 0.0 ? batches * (c.batch + c.lane_draw * rounds * (domain / (double)pool) * (lane > 1.0 ? lane : 1.0)) : 0.0;
+    const double walk = batches * (c.batch + c.lane_draw * rounds * (domain / (double)pool) * (lane > 1.0 ? lane : 1.0));
+    const double heaviest = (d.most > 0.0 ? walk : 0.0) + c.keys * (double)pool / 65536.0;
     const double mean = p.mode == 0 ? d.mean : d.mean + c.uneven * (d.most - d.mean);
     const double rows = 1e-3 * (double)p.heads * (double)p.nq;
     return c.base + heaviest * (1.0 + c.head * (p.heads - 1) * (p.nq < 8192 ? p.nq / 8192.0 : 1.0)) +
@@ -1085,25 +1087,27 @@ double form_us(const MaskParams& p, const RowDraws& d, const FormCost& c) {
 // seeds, 40 draws each, 139 us by waves, 81 in the grid; 591 rows of 150 seeds to 59
 // draws 69 and 51; 8 heads of 22,781 rows of 70 seeds to 228 draws 3,890 and 3,530),
 // and the workgroups are faster than the grid where rows are few (0.6 to 0.9 of its
-// time to 2,048 rows).  Of the 4,800 builds 20 are more than 3% slower than in the
+// time to 2,048 rows).  Of the 6,000 builds 27 are more than 3% slower than in the
 // grid with two rows to a ticket; with waves wherever rows are light one in twenty
 // was, some by half.
 enum class OnePass { kWaves, kChunks, kGrid };
 OnePass one_pass_form(const MaskParams& p, const RowDraws& d) {
-    const double waves = 0.5 + form_us(p, d, {64, 9.0, 3.6, 0.215, 0.5, 1.8, 0.8, 0.5, 0.125, 0.15});
-    const double chunks = form_us(p, d, {256, 7.3, 3.05, 0.21, 0.27, 11.4, 8.5, 0.43, 0.064, 0.1});
-    const double grid = form_us(p, d, {256, 8.7, 3.2, 0.19, 0.0, 12.0, 18.5, 0.15, 0.047, 0.0});
+    const double waves = 0.5 + form_us(p, d, {64, 9.0, 3.6, 0.215, 0.5, 1.8, 0.8, 0.5, 0.125, 0.15, 5.0});
+    const double chunks = form_us(p, d, {256, 7.3, 3.05, 0.21, 0.27, 11.4, 8.5, 0.43, 0.064, 0.1, 0.0});
+    const double grid = form_us(p, d, {256, 8.7, 3.2, 0.19, 0.0, 12.0, 18.5, 0.15, 0.047, 0.0, 0.0});
     return waves <= chunks && waves <= grid ? OnePass::kWaves : chunks <= grid ? OnePass::kChunks : OnePass::kGrid;
 }
 
 // Two-phase build, likewise: 32,768 rows to 2,870 draws 205 us by waves and 290 by
-// workgroups, 512 rows of 8,190 draws 31 and 16.  Of the 4,800 count phases 10 are
-// more than 7% slower than by workgroups alone.
+// workgroups, 512 rows of 8,190 draws 31 and 16.  Structural rows count more towards
+// their heaviest (31,000 rows of 100 seeds, 31 draws each and 155 at most: 370 and
+// 271): of 700 such builds 4 are more than 3% slower than by workgroups alone, 41
+// where they count by the mean.  Of all 6,000 count phases 10 are more than 7% slower.
 bool two_phase_waves(const MaskParams& p) {
-    if (middle_draws(p) >= kWaveDraws || group_smem_bytes<64>(p, kThreads / 64) > kWaveSmemTwoPhase) return false;
+    if (middle_draws(p) >= kWaveDraws || bitmap_words(p) > kWaveKeysTwoPhase / 32) return false;
     const RowDraws d = row_draws(p);
-    return 1.0 + form_us(p, d, {64, 4.8, 4.0, 0.12, 0.0, 0.75, 0.0, 0.85, 0.076, 0.025}) <=
-           form_us(p, d, {256, 4.8, 3.13, 0.187, 0.0, 1.1, 0.0, 2.55, 0.087, 0.0});
+    return 1.0 + form_us(p, d, {64, 4.8, 4.0, 0.12, 0.0, 0.75, 0.0, 0.85, 0.076, 0.2, 1.7}) <=
+           form_us(p, d, {256, 4.8, 3.13, 0.187, 0.0, 1.1, 0.0, 2.55, 0.087, 0.0, 0.0});
 }
 
 }  // namespace

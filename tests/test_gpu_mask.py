@@ -292,6 +292,8 @@ DISPATCH = [
     (1, 50_000, 2000, 1, 100, 64, 33, 4, 0, 2000),      # Structural by 256 lanes
     (1, 10_000, 4097, 2, 70, 64, 33, 4, 0, 4097),       # by 8 waves, two seed batches of 35 to a wave
     (0, 100, 100000, 1, 3, 0, 0, 0, 95000, 4093),       # 100,000 keys: 4 waves, a last chunk of one row
+    (0, 100, 65537, 1, 3, 0, 0, 0, 61436, 4100),        # pools to 65,536 keys: waves in two phases
+    (0, 100, 65537, 1, 3, 0, 0, 0, 61437, 4100),        # one more: workgroups
     (0, 1_000, 5001, 2, 100, 0, 0, 0, 0, 5001),         # rows enough for waves in two phases, two batches of seeds
     (0, 1_000, 5001, 1, 100, 0, 0, 0, 1801, 3200),      # fewer: workgroups in two phases
     (1, 20_000, 3000, 2, 30, 64, 0, 0, 0, 3000),        # Structural, uneven rows: waves in two phases
